@@ -205,30 +205,61 @@ __global__ __launch_bounds__(CB_THREADS, 2) void k_combine32(CombineArgs c) {
 }
 
 // A few states (a one-step prediction, Sec. 2.3's u(t + dt)): bound by the
-// read of the stored columns, not by the flops.  One row per lane (a wave
-// reads 64 consecutive rows of a column, one 64-row tile), the coefficients
-// of each state uniform across the wave (scalar loads); the stored values
-// are read once for all the states of the launch.
+// read of the stored columns, not by the flops.  A lane reads 8 bytes of a
+// column (one FP64, two FP32 or four BF16 rows), so a wave reads 512 bytes
+// of every column, and the coefficients of each state are uniform across
+// the wave (scalar loads); the stored values are read once for all the
+// states of the launch.  For FP32 and BF16
+// storage every column's load is issued before the first value is used, and
+// without a test (a column past the m live ones re-reads column 0, a cache
+// hit, against a zero coefficient; stored values are finite): with the load
+// and its conversion under a test per column, each column waited for the
+// one before.  One state at n = 6M with 72 columns: FP32 997 -> 294 us
+// (5.9 TB/s), BF16 782 -> 134 us (6.4 TB/s); FP64, which needs no
+// conversion and keeps the test (it skips the loads of a short bucket), 595 us
+// (5.8 TB/s).
 constexpr int CR_KMAX = 4;
 template <typename TS, typename TO, int RB>
-__global__ __launch_bounds__(256) void k_combine_rows(CombineArgs c) {
-  const DevState* __restrict__ st = c.st;
-  const int m = st->m;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= c.n) return;
-  const TS* __restrict__ T = static_cast<const TS*>(c.Us) + (i >> 6) * (int64_t)c.ct * 64 + (i & 63);
-  double u[RB];
+__device__ __forceinline__ void combine_rows_body(const CombineArgs& c, const int64_t blk) {
+  typedef Storage<TS> SC;
+  constexpr int RPL = 8 / (int)sizeof(TS);   // rows per lane
+  const int m = c.st->m;
+  const int64_t row0 = (blk * 256 + threadIdx.x) * RPL;   // 64 / RPL lanes per tile
+  if (row0 >= c.n) return;
+  // (rows of the last tile past n exist and are zero)
+  const gbytes T = (gbytes)(static_cast<const TS*>(c.Us) + (row0 >> 6) * (int64_t)c.ct * 64 + (row0 & 63));
+  uint64_t u[RB];
 #pragma unroll
-  for (int j = 0; j < RB; ++j) u[j] = j < m ? Storage<TS>::to_double(T[j * 64]) : 0.0;
+  for (int j = 0; j < RB; ++j) {
+    if constexpr (RPL > 1) u[j] = gload8(T + (j < m ? j : 0) * 64 * (int)sizeof(TS));
+    else u[j] = j < m ? gload8(T + j * 64 * (int)sizeof(TS)) : 0;
+  }
   typedef const __attribute__((address_space(4))) double* cdp;
-  cdp A = (cdp)st->coefA;
+  cdp A = (cdp)c.st->coefA;
   TO* __restrict__ out = static_cast<TO*>(c.out);
   for (int k = 0; k < c.K; ++k) {
-    double acc = 0.0;
+    double acc[RPL];
 #pragma unroll
-    for (int j = 0; j < RB; ++j) acc = __builtin_fma(u[j], A[k * CMAX + j], acc);
-    out[(int64_t)k * c.ldo + i] = (TO)acc;
+    for (int e = 0; e < RPL; ++e) acc[e] = 0.0;
+#pragma unroll
+    for (int j = 0; j < RB; ++j) {
+      const double a = A[k * CMAX + j];
+      // (an empty asm statement that claims to change the packed rows: the
+      // conversions stay here, not hoisted out of the loop over the states,
+      // where they would hold every row of every column in FP64)
+      if constexpr (RPL > 1) asm volatile("" : "+v"(u[j]));
+#pragma unroll
+      for (int e = 0; e < RPL; ++e) acc[e] = __builtin_fma(SC::to_double(SC::elem(u[j], e)), a, acc[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < RPL; ++e)
+      if (row0 + e < c.n) out[(int64_t)k * c.ldo + row0 + e] = (TO)acc[e];
   }
+}
+
+template <typename TS, typename TO, int RB>
+__global__ __launch_bounds__(256) void k_combine_rows(CombineArgs c) {
+  combine_rows_body<TS, TO, RB>(c, blockIdx.x);
 }
 
 // Workgroups of kernel f the GPU holds at once (its occupancy per CU times
@@ -299,7 +330,8 @@ static hipError_t launch_ns32(const CombineArgs& c, int rb, hipStream_t s) {
 
 template <typename TS, typename TO>
 static hipError_t launch_rows(const CombineArgs& c, int rb, hipStream_t s) {
-  const dim3 grid((unsigned)((c.n + 255) / 256)), block(256);
+  const int64_t rows = 256 * (8 / (int)sizeof(TS));   // rows per workgroup
+  const dim3 grid((unsigned)((c.n + rows - 1) / rows)), block(256);
   switch (rb) {
 #define ODMD_CASE(RB) \
   case RB: hipLaunchKernelGGL((k_combine_rows<TS, TO, RB>), grid, block, 0, s, c); break;
