@@ -3,12 +3,12 @@
 // Sec. 2.3: A~ = V Lambda V^-1 and Phi = U V (the projected DMD modes), and
 // the prediction u(t) = Phi Lambda^(t/dt) Phi^+ u(0).
 //
-// k_eig (one 64-lane wavefront, FP64), on demand for the eigenpairs:
+// k_eig (one workgroup, FP64), on demand for the eigenpairs:
 //   1. Householder reduction of A~ to upper Hessenberg form H = Q^T A~ Q;
 //   2. Francis double-shift QR iteration to the real Schur form T = Z^T A~ Z
 //      (1x1 and standardised 2x2 diagonal blocks), accumulating Z;
-//   3. eigenvectors of T by back-substitution (complex arithmetic), one lane
-//      per eigenvalue, then V = Z X, unit 2-norm, largest entry real > 0;
+//   3. eigenvectors of T by back-substitution (complex arithmetic), eight
+//      lanes per eigenvalue, then V = Z X, unit 2-norm, largest entry real > 0;
 //   4. order by |lambda| descending, then Im descending.
 // k_power_coef: the prediction's coefficients for a chunk of steps, as
 // powers of A~ applied to U^T x_a (equal to the eigenvector form at integer
@@ -19,6 +19,7 @@
 
 #include "odmd_internal.h"
 #include "pass.h"
+#include "xlane.h"
 
 namespace odmd {
 
@@ -47,6 +48,15 @@ __device__ __forceinline__ double cabs2(cplx a) { return hypot(a.re, a.im); }
 #define Hm(i, j) H[(j) * LDH + (i)]
 #define Zm(i, j) Z[(j) * LDH + (i)]
 
+// LDS written by some lanes of a wavefront is read by others of it next (the
+// wavefront's LDS operations complete in order; the fence keeps the compiler
+// from reordering them)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The value of v in the given lane (a wave-uniform index), in every lane.
 __device__ __forceinline__ double readlane_d(double v, int lane) {
   const long long b = __double_as_longlong(v);
@@ -55,230 +65,215 @@ __device__ __forceinline__ double readlane_d(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// 1/x and 1/sqrt(x): hardware estimates refined by two Newton steps each
-__device__ __forceinline__ double recip_n(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
-  r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
-  return r;
-}
-__device__ __forceinline__ double rsqrt_n(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  double h = 0.5 * x;
-  r = r * __builtin_fma(-h * r, r, 1.5);
-  r = r * __builtin_fma(-h * r, r, 1.5);
-  return r;
-}
-
-// Reflector mapping (x, y, z) to (alpha, 0, 0): v = (1, v1, v2), tau.
-__device__ __forceinline__ bool make_reflector(double x, double y, double z, double& tau,
-                                               double& v1, double& v2, double& alpha) {
-  if (y == 0.0 && z == 0.0) return false;
-  double ss = __builtin_fma(z, z, __builtin_fma(y, y, x * x));
-  double sc = 1.0;
-  if (!(ss > 0x1p-960 && ss < 0x1p960)) {     // rescale (rare): avoid under/overflow
-    sc = fmax(fabs(x), fmax(fabs(y), fabs(z)));
-    const double isc = 1.0 / sc;
-    x *= isc;
-    y *= isc;
-    z *= isc;
-    ss = __builtin_fma(z, z, __builtin_fma(y, y, x * x));
-  }
-  const double rn = rsqrt_n(ss);               // 1 / ||(x, y, z)||
-  double nrm = ss * rn;
-  nrm = __builtin_fma(0.5 * rn, __builtin_fma(-nrm, nrm, ss), nrm);
-  const double al = x >= 0.0 ? -nrm : nrm;
-  const double id = recip_n(x - al);           // |x - al| = |x| + nrm
-  v1 = y * id;
-  v2 = z * id;
-  tau = __builtin_fma(fabs(x), rn, 1.0);       // (al - x) / al = 1 + |x| / nrm
-  alpha = al * sc;
-  return true;
+// Householder reflector P = I - beta w w^T mapping (x, y, z) to (alpha, 0, 0),
+// w = (w0, y, z): with nrm = ||(x, y, z)|| and alpha = -sign(x) nrm,
+// w0 = x - alpha and beta = 2 / w.w = 1 / (nrm (nrm + |x|)).  Its dependent
+// chain is the bulge chase's: nrm by one Goldschmidt step from the hardware
+// estimate (2^-24 relative, then 2^-47) and a residual correction, beta by a
+// third-order step from the reciprocal estimate of the uncorrected
+// denominator, which runs beside the correction; the products with w run
+// beside beta.  No branch: the matrix is scaled to entries of order one, so
+// nothing overflows, and a vector whose square underflows to below 2^-900 is
+// zero for it (the identity, y and z dropped).
+struct Reflector {
+  double w0, w1, w2, beta, alpha;
+};
+__device__ __forceinline__ Reflector make_reflector(double x, double y, double z) {
+  constexpr double TINY = 0x1p-900;
+  const double s0 = __builtin_fma(z, z, __builtin_fma(y, y, x * x));
+  const bool ok = s0 > TINY;
+  const double ss = fmax(s0, TINY);
+  const double rn = __builtin_amdgcn_rsq(ss);
+  double g = ss * rn, h = 0.5 * rn;            // nrm, 1 / (2 nrm)
+  const double rd = __builtin_amdgcn_rcp(__builtin_fma(g, fabs(x), ss));
+  const double e = __builtin_fma(-g, h, 0.5);
+  g = __builtin_fma(g, e, g);
+  h = __builtin_fma(h, e, h);
+  g = __builtin_fma(__builtin_fma(-g, g, ss), h, g);
+  const double den = __builtin_fma(g, fabs(x), ss);
+  const double f = __builtin_fma(-den, rd, 1.0);
+  const double al = x >= 0.0 ? -g : g;
+  Reflector R;
+  R.w0 = x - al;
+  R.w1 = y;
+  R.w2 = z;
+  R.beta = ok ? __builtin_fma(rd, __builtin_fma(f, f, f), rd) : 0.0;
+  R.alpha = ok ? al : x;
+  return R;
 }
 
-// One step of the double-shift bulge chase: the reflector P = I - tau v v^T
-// (v = (1, v1, v2); (1, v1) for the last step, THREE false) built from
-// (x, y, z), applied as H <- P H P and Z <- Z P.  Every lane t is column t of
-// the left application (rows k .. k+2, columns [c0, n) outside the 3 x 3
-// block), row t of the right one (columns k .. k+2, rows [0, r1]) and row t
-// of Z's.  Rows k .. k+2 meet both: those lanes apply the left reflector to
-// their row of the 3 x 3 block (read by every lane) before the right one,
-// and the column lanes leave the block to them, so no entry is written
-// twice.  A lane outside a role reads and writes its own slots of dum
-// instead (straight-line code, no divergent branches).  Returns this lane's
-// new H(t, k) (rows <= r1), from which the next step's (x, y, z) are taken.
-template <bool THREE, bool VECS>
-__device__ __forceinline__ double bulge_step(double* H, double* Z, double* dum, int n, int l, int hi,
-                                             int k, double x, double y, double z) {
-  constexpr int nb = THREE ? 3 : 2;
-  const int t = threadIdx.x;
-  const int c0 = k > l ? k - 1 : l;
-  const int r1 = THREE ? min(k + 3, hi) : hi;
-  const bool col_live = t >= c0 && t < n && (t < k || t >= k + nb);
-  const bool row_live = t <= r1;
-  const bool z_live = t < n;
-  double* pc = col_live ? &Hm(k, t) : dum + 9 * t;          // rows k .. k+nb-1, stride 1
-  double* pr0 = row_live ? &Hm(t, k) : dum + 9 * t + 3;
-  double* pr1 = row_live ? &Hm(t, k + 1) : dum + 9 * t + 4;
-  double* pr2 = row_live ? &Hm(t, k + 2) : dum + 9 * t + 5;
-  double* pz0 = z_live ? &Zm(t, k) : dum + 9 * t + 6;
-  double* pz1 = z_live ? &Zm(t, k + 1) : dum + 9 * t + 7;
-  double* pz2 = z_live ? &Zm(t, k + 2) : dum + 9 * t + 8;
-  double b0[nb], b1[nb], b2[nb];                             // H(k .. k+2, k + c)
-#pragma unroll
-  for (int c = 0; c < nb; ++c) {
-    b0[c] = Hm(k, k + c);
-    b1[c] = Hm(k + 1, k + c);
-    b2[c] = THREE ? Hm(k + 2, k + c) : 0.0;
-  }
-  double cv0 = pc[0], cv1 = pc[1], cv2 = THREE ? pc[2] : 0.0;
-  double rv0 = *pr0, rv1 = *pr1, rv2 = THREE ? *pr2 : 0.0;
-  double zv0 = VECS ? *pz0 : 0.0, zv1 = VECS ? *pz1 : 0.0, zv2 = VECS && THREE ? *pz2 : 0.0;
-  double tau, v1, v2 = 0.0, al;
-  if (!make_reflector(x, y, THREE ? z : 0.0, tau, v1, v2, al)) return rv0;   // uniform
-  // column t, rows k .. k+2 (the bulge column k - 1 becomes (alpha, 0, 0))
-  const double sc = tau * (cv0 + v1 * cv1 + v2 * cv2);
-  const bool bulge = k > l && t == k - 1;
-  cv0 = bulge ? al : cv0 - sc;
-  cv1 = bulge ? 0.0 : cv1 - sc * v1;
-  cv2 = bulge ? 0.0 : cv2 - sc * v2;
-  // rows k .. k+2: row t of the block after the left application
-  const int a = t - k;
-  const bool in_blk = a >= 0 && a < nb;
-  const double va = a == 1 ? v1 : (a == 2 ? v2 : 1.0);
-#pragma unroll
-  for (int c = 0; c < nb; ++c) {
-    const double sb = tau * (b0[c] + v1 * b1[c] + v2 * b2[c]);
-    const double ba = a == 1 ? b1[c] : (a == 2 ? b2[c] : b0[c]);
-    const double nr = ba - sb * va;
-    if (c == 0) rv0 = in_blk ? nr : rv0;
-    if (c == 1) rv1 = in_blk ? nr : rv1;
-    if (c == 2) rv2 = in_blk ? nr : rv2;
-  }
-  // row t, columns k .. k+2, and row t of Z
-  const double sr = tau * (rv0 + v1 * rv1 + v2 * rv2);
-  rv0 -= sr;
-  rv1 -= sr * v1;
-  rv2 -= sr * v2;
-  if (VECS) {
-    const double sz = tau * (zv0 + v1 * zv1 + v2 * zv2);
-    zv0 -= sz;
-    zv1 -= sz * v1;
-    zv2 -= sz * v2;
-  }
-  pc[0] = cv0;
-  pc[1] = cv1;
-  if (THREE) pc[2] = cv2;
-  *pr0 = rv0;
-  *pr1 = rv1;
-  if (THREE) *pr2 = rv2;
-  if (VECS) {
-    *pz0 = zv0;
-    *pz1 = zv1;
-    if (THREE) *pz2 = zv2;
-  }
-  return rv0;
+// k_eig's workgroup: wavefronts 0 .. EIG_K-1 carry one bulge each, with
+// vectors as many more apply the reflectors to Z; the reduction and the
+// eigenvectors use all of them.
+constexpr int EIG_K = 4;
+constexpr int EIG_GAP = 3;               // rows between neighbouring bulges
+constexpr int EIG_MIN = 5;               // active rows per bulge, at least
+template <bool VECS>
+constexpr int eig_threads() { return (VECS ? 2 : 1) * EIG_K * 64; }
+
+// sum over groups of eight neighbouring lanes (every lane gets it)
+__device__ __forceinline__ double sum8(double v) {
+  v += dpp_move<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+  v += dpp_move<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+  v += dpp_move<0x141>(v);   // row_half_mirror
+  return v;
 }
 
 // VECS false: eigenvalues only (no Z, eigenvectors or V); the cache level
-// eig_valid is 1 after such a call and 2 after a call with vectors.
+// eig_valid is 1 after such a call and 2 after a call with vectors.  Both
+// run the same operations on H, so the eigenvalues are the same bit for bit.
+//
+// Latency bounds it: one workgroup, a serial chain of reflectors.  The chain
+// is cut in three ways.  (1) EIG_K bulges are chased at once, EIG_GAP rows
+// apart, one wavefront each, all with the shifts of the trailing 2 x 2 block:
+// a group of K sweeps over N rows takes N - 1 + 3 (K - 1) steps instead of
+// K (N - 1), for about 1.4 times the sweeps (the K sweeps share their
+// shifts, so a group converges with order K + 1 instead of 2^K).  (2) A step
+// has two phases, a barrier after each: every bulge applies its reflector
+// to its three rows (lane t is column t), then to its three columns (lane t
+// is row t).  H is zero below the bulges and padded with zero rows and
+// columns, so no lane is masked and no entry of the 3 x 3 block is formed
+// twice.  (3) Z's columns are left to wavefronts of their own, and the
+// reduction and eigenvector sums are split over the workgroup.
+// A~ of rank 40 (n = 160,000 wake): 415 us (854 with one wavefront and one
+// bulge); with vectors at rank 64: 1137 us (2388).  A step takes about 840
+// cycles (1160 before; one bulge alone 630), with vectors 1030.
 template <bool VECS>
 __device__ __forceinline__ void eig_body(DevState* st) {
   if (st->eig_valid >= (VECS ? 2 : 1)) return;
-  __shared__ double H[RMAX * LDH];
-  __shared__ double Z[RMAX * LDH];
-  __shared__ double Xr[(RMAX + 1) * LDH];
-  __shared__ double Xi[(RMAX + 1) * LDH];
-  __shared__ double wr[RMAX], wi[RMAX], hv[RMAX];
-  __shared__ double dum[64 * 9];           // slots of lanes outside a role of a bulge step
-  __shared__ int sfail;
-  const int t = threadIdx.x;
+  constexpr int NTH = eig_threads<VECS>();
+  __shared__ double H[(RMAX + 2) * LDH];         // zero past n x n
+  __shared__ double Z[VECS ? (RMAX + 2) * LDH : 1];
+  __shared__ double Xr[VECS ? (RMAX + 1) * LDH : 1];
+  __shared__ double Xi[VECS ? (RMAX + 1) * LDH : 1];
+  __shared__ double wr[RMAX], wi[RMAX], red[EIG_K][RMAX];
+  __shared__ double redb[NTH / 64][RMAX];
+  __shared__ Reflector rf[EIG_K][2];
+  __shared__ int pos[RMAX];
+  const int tid = threadIdx.x, t = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = st->r;
   if (n == 0) {
-    if (t == 0) {
+    if (tid == 0) {
       st->eig_valid = 2;
       st->eig_status = 0;
     }
     return;
   }
-  for (int idx = t; idx < n * n; idx += 64) {
-    const int i = idx % n, j = idx / n;
-    Hm(i, j) = st->At[j * RMAX + i];
-    if (VECS) Zm(i, j) = (i == j) ? 1.0 : 0.0;
-  }
-  if (t == 0) sfail = 0;
-  __syncthreads();
-
-  // 1. Hessenberg reduction
-  for (int k = 0; k + 2 < n; ++k) {
-    double x2 = 0.0;
-    if (t > k + 1 && t < n) x2 = Hm(t, k) * Hm(t, k);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x2 += __shfl_xor(x2, o, 64);
-    const double x0 = Hm(k + 1, k);
-    if (x2 == 0.0) {
-      __syncthreads();
-      continue;
-    }
-    const double nrm = sqrt(x0 * x0 + x2);
-    const double al = x0 >= 0.0 ? -nrm : nrm;
-    const double v0 = x0 - al;
-    const double beta = 2.0 / (v0 * v0 + x2);
-    if (t < n) hv[t] = (t == k + 1) ? v0 : (t > k + 1 ? Hm(t, k) : 0.0);
-    __syncthreads();
-    if (t >= k && t < n) {          // left: rows k+1.., column t
-      double s = 0.0, s2 = 0.0;
-      int i = k + 1;
-#pragma unroll 4
-      for (; i + 1 < n; i += 2) {
-        s = __builtin_fma(hv[i], Hm(i, t), s);
-        s2 = __builtin_fma(hv[i + 1], Hm(i + 1, t), s2);
-      }
-      if (i < n) s = __builtin_fma(hv[i], Hm(i, t), s);
-      s = (s + s2) * beta;
-#pragma unroll 8
-      for (int i = k + 1; i < n; ++i) Hm(i, t) -= s * hv[i];
-    }
-    __syncthreads();
-    if (t < n) {                    // right: columns k+1.., row t (H and Z)
-      double s = 0.0, sz = 0.0, s2 = 0.0, sz2 = 0.0;
-      int j = k + 1;
-#pragma unroll 4
-      for (; j + 1 < n; j += 2) {
-        s = __builtin_fma(Hm(t, j), hv[j], s);
-        s2 = __builtin_fma(Hm(t, j + 1), hv[j + 1], s2);
-        if (VECS) {
-          sz = __builtin_fma(Zm(t, j), hv[j], sz);
-          sz2 = __builtin_fma(Zm(t, j + 1), hv[j + 1], sz2);
-        }
-      }
-      if (j < n) {
-        s = __builtin_fma(Hm(t, j), hv[j], s);
-        if (VECS) sz = __builtin_fma(Zm(t, j), hv[j], sz);
-      }
-      s = (s + s2) * beta;
-      sz = (sz + sz2) * beta;
-#pragma unroll 8
-      for (int j = k + 1; j < n; ++j) {
-        Hm(t, j) -= s * hv[j];
-        if (VECS) Zm(t, j) -= sz * hv[j];
-      }
-    }
-    __syncthreads();
-    if (t > k + 1 && t < n) Hm(t, k) = 0.0;
-    if (t == 0) Hm(k + 1, k) = al;
-    __syncthreads();
-  }
-
-  // norm for deflation tests on zero diagonals
+  // A~ scaled by a power of two to entries of order one (exact), zero past n
   double hn = 0.0;
-  for (int idx = t; idx < n * n; idx += 64) hn = fmax(hn, fabs(Hm(idx % n, idx / n)));
+  constexpr int NL = RMAX * RMAX / NTH;
+  double av[NL];                         // every load in flight at once
+#pragma unroll
+  for (int u = 0; u < NL; ++u) {
+    const int i = t, j = wave + u * (NTH / 64);
+    const bool in = i < n && j < n;
+    const double v = st->At[in ? j * RMAX + i : 0];
+    av[u] = in ? v : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < NL; ++u) hn = fmax(hn, fabs(av[u]));
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) hn = fmax(hn, __shfl_xor(hn, o, 64));
-  if (hn == 0.0) hn = 1.0;
+  if (t == 0) red[0][wave] = hn;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NTH / 64; ++w) hn = fmax(hn, red[0][w]);
+  const int ex = hn > 0.0 && hn < INFINITY ? ilogb(hn) : 0;
+  // row RMAX and the columns past RMAX are zero too
+  for (int idx = tid; idx < 2 * LDH; idx += NTH) H[RMAX * LDH + idx] = 0.0;
+  if (tid < RMAX) H[tid * LDH + RMAX] = 0.0;
+#pragma unroll
+  for (int u = 0; u < NL; ++u) H[(wave + u * (NTH / 64)) * LDH + t] = ldexp(av[u], -ex);
+  if (VECS) {                            // Z's columns past RMAX (their values are not used)
+    for (int idx = tid; idx < 2 * LDH; idx += NTH) Z[RMAX * LDH + idx] = 0.0;
+  }
+  hn = hn > 0.0 && hn < INFINITY ? ldexp(hn, -ex) : 1.0;
+  __syncthreads();
 
-  // 2. Francis double-shift QR to real Schur form
+  // 1. Hessenberg reduction.  Both sides of a reflector I - beta v v^T in one
+  //    update from the old H, with a = beta H^T v, b = beta H v and
+  //    c = b - beta (v.b) v:  H <- H - v a^T - c v^T; and Z <- Z - (beta Z v) v^T.
+  //    The first EIG_K wavefronts take H: thread (t, part) keeps the entries
+  //    H(part + EIG_K e, t) in registers (the column sums and the update need
+  //    no LDS reads, which bounded this phase) and writes them to LDS, where
+  //    the row sums read them; with vectors the others take Z, thread
+  //    (t, part) the entries Z(t, part + EIG_K e).  v_i and c_i come from
+  //    lane i's register.
+  const int part = wave & (EIG_K - 1);
+  const bool onH = !VECS || wave < EIG_K;
+  constexpr int NE1 = RMAX / EIG_K;
+  double own[NE1];
+#pragma unroll
+  for (int e = 0; e < NE1; ++e)
+    own[e] = onH ? Hm(part + EIG_K * e, t) : (t == part + EIG_K * e ? 1.0 : 0.0);
+  for (int k = 0; k + 2 < n; ++k) {
+    const double hk = Hm(t, k);
+    double x2 = t > k + 1 ? hk * hk : 0.0;
+    x2 = add_half_pair(add_row_pair(row_sum(x2)));
+    const double x0 = readlane_d(hk, k + 1);
+    const bool none = x2 <= 0x1p-900;    // uniform: nothing to annihilate
+    const double nrm = none ? fabs(x0) : sqrt(__builtin_fma(x0, x0, x2));
+    const double al = none ? x0 : (x0 >= 0.0 ? -nrm : nrm);
+    const double beta = none ? 0.0 : 1.0 / (nrm * (nrm + fabs(x0)));
+    const double vt = none ? 0.0 : (t == k + 1 ? x0 - al : (t > k + 1 ? hk : 0.0));
+    double a = 0.0, a2 = 0.0, b = 0.0, b2 = 0.0;
+    if (onH) {
+      double m[NE1];                     // row t
+#pragma unroll
+      for (int e = 0; e < NE1; ++e) m[e] = Hm(t, part + EIG_K * e);
+#pragma unroll
+      for (int e = 0; e < NE1; e += 2) {
+        const double v0 = readlane_d(vt, part + EIG_K * e), v1 = readlane_d(vt, part + EIG_K * (e + 1));
+        a = __builtin_fma(v0, own[e], a);
+        a2 = __builtin_fma(v1, own[e + 1], a2);
+        b = __builtin_fma(v0, m[e], b);
+        b2 = __builtin_fma(v1, m[e + 1], b2);
+      }
+      red[part][t] = a + a2;
+    } else {
+#pragma unroll
+      for (int e = 0; e < NE1; e += 2) {
+        b = __builtin_fma(readlane_d(vt, part + EIG_K * e), own[e], b);
+        b2 = __builtin_fma(readlane_d(vt, part + EIG_K * (e + 1)), own[e + 1], b2);
+      }
+    }
+    redb[wave][t] = b + b2;
+    __syncthreads();
+    a = b = 0.0;
+#pragma unroll
+    for (int p = 0; p < EIG_K; ++p) {
+      a += red[p][t];
+      b += redb[(wave & ~(EIG_K - 1)) + p][t];
+    }
+    a *= beta;
+    b *= beta;
+    if (onH) {
+      const double vb = add_half_pair(add_row_pair(row_sum(vt * b)));
+      const double ct = __builtin_fma(-beta * vb, vt, b);
+      const bool colk = t == k;          // its entries are al and zeros by construction
+#pragma unroll
+      for (int e = 0; e < NE1; ++e) {
+        const int i = part + EIG_K * e;
+        const double g = __builtin_fma(-readlane_d(ct, i), vt, __builtin_fma(-readlane_d(vt, i), a, own[e]));
+        own[e] = colk && i > k ? (i == k + 1 ? al : 0.0) : g;
+        Hm(i, t) = own[e];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < NE1; ++e) own[e] = __builtin_fma(-b, readlane_d(vt, part + EIG_K * e), own[e]);
+    }
+    __syncthreads();
+  }
+  if (VECS && !onH) {
+#pragma unroll
+    for (int e = 0; e < NE1; ++e) Zm(t, part + EIG_K * e) = own[e];
+  }
+
+  // 2. Francis double-shift QR to real Schur form.  Every wavefront takes
+  //    the same decisions from the same H.
   int hi = n - 1, its = 0, total = 0;
+  bool fail = false;
   while (hi >= 0) {
     // l = the largest index in [1, hi] whose subdiagonal entry is
     // negligible, else 0: every lane tests one entry, one ballot
@@ -291,117 +286,175 @@ __device__ __forceinline__ void eig_body(DevState* st) {
     const unsigned long long mask = __ballot(neg);
     const int l = mask ? 63 - __builtin_clzll(mask) : 0;
     __syncthreads();
-    if (l > 0 && t == 0) Hm(l, l - 1) = 0.0;
-    __syncthreads();
+    if (l > 0 && tid == 0) Hm(l, l - 1) = 0.0;
     if (l == hi) {
-      if (t == 0) {
+      if (tid == 0) {
         wr[hi] = Hm(hi, hi);
         wi[hi] = 0.0;
       }
       --hi;
       its = 0;
-      continue;
+      continue;                          // (the entry just cleared is not read below hi)
     }
     if (l == hi - 1) {
       const int p = hi - 1, q = hi;
       const double a = Hm(p, p), b = Hm(p, q), c = Hm(q, p), d = Hm(q, q);
       const double pp = 0.5 * (a - d);
       const double disc = pp * pp + b * c;
+      __syncthreads();
       if (disc >= 0.0) {
         const double sq = sqrt(disc);
         const double zz = pp + (pp >= 0.0 ? sq : -sq);
         double la = d + zz, lb = (zz != 0.0) ? d - b * c / zz : d;
         // rotation whose first column is the eigenvector (zz, c) of la
         const double h = hypot(zz, c);
-        __syncthreads();
         if (h > 0.0) {
           const double cs = zz / h, sn = c / h;
-          if (t >= p && t < n) {      // rows p, q from the left (G^T)
+          if (wave == 0 && t >= p && t < n) {      // rows p, q from the left (G^T)
             const double u = Hm(p, t), v = Hm(q, t);
             Hm(p, t) = cs * u + sn * v;
             Hm(q, t) = -sn * u + cs * v;
           }
           __syncthreads();
-          if (t <= q) {               // columns p, q from the right
+          if (wave == 0 && t <= q) {               // columns p, q from the right
             const double u = Hm(t, p), v = Hm(t, q);
             Hm(t, p) = cs * u + sn * v;
             Hm(t, q) = -sn * u + cs * v;
           }
-          if (VECS && t < n) {
+          if (VECS && wave == EIG_K && t < n) {
             const double u = Zm(t, p), v = Zm(t, q);
             Zm(t, p) = cs * u + sn * v;
             Zm(t, q) = -sn * u + cs * v;
           }
           __syncthreads();
-          if (t == 0) Hm(q, p) = 0.0;
+          if (tid == 0) Hm(q, p) = 0.0;
           la = Hm(p, p);
           lb = Hm(q, q);
-          __syncthreads();
         }
-        if (t == 0) {
+        if (tid == 0) {
           wr[p] = la;
           wi[p] = 0.0;
           wr[q] = lb;
           wi[q] = 0.0;
         }
-      } else {
-        if (t == 0) {
-          wr[p] = wr[q] = a - pp;        // (a + d) / 2
-          wi[p] = sqrt(-disc);
-          wi[q] = -sqrt(-disc);
-        }
+      } else if (tid == 0) {
+        wr[p] = wr[q] = a - pp;          // (a + d) / 2
+        wi[p] = sqrt(-disc);
+        wi[q] = -sqrt(-disc);
       }
-      __syncthreads();
       hi -= 2;
       its = 0;
       continue;
     }
     if (total >= 30 * n) {
-      if (t == 0) sfail = 1;
+      fail = true;
       break;
     }
     ++its;
     ++total;
+    const int N = hi - l + 1;            // at least 3
+    int K = min(EIG_K, max(1, N / EIG_MIN));
     double s, tt;
-    if (its == 10 || its == 20) {     // exceptional shift
+    if (its == 10 || its == 20) {        // exceptional shift
       const double w = fabs(Hm(hi, hi - 1)) + fabs(Hm(hi - 1, hi - 2));
       s = 1.5 * w;
       tt = w * w;
+      K = 1;
     } else {
       s = Hm(hi - 1, hi - 1) + Hm(hi, hi);
       tt = Hm(hi - 1, hi - 1) * Hm(hi, hi) - Hm(hi - 1, hi) * Hm(hi, hi - 1);
     }
-    double x = Hm(l, l) * Hm(l, l) + Hm(l, l + 1) * Hm(l + 1, l) - s * Hm(l, l) + tt;
-    double y = Hm(l + 1, l) * (Hm(l, l) + Hm(l + 1, l + 1) - s);
-    double z = Hm(l + 1, l) * Hm(l + 2, l + 1);
-    // Bulge chase: one barrier per step; the next step's (x, y, z), the new
-    // H(k+1 .. k+3, k), come from the registers of the lanes of those rows.
-    for (int k = l; k < hi - 1; ++k) {
-      const double colk = bulge_step<true, VECS>(H, Z, dum, n, l, hi, k, x, y, z);
-      x = readlane_d(colk, k + 1);
-      y = readlane_d(colk, k + 2);
-      z = (k + 3 <= hi) ? readlane_d(colk, k + 3) : 0.0;
-      __syncthreads();
+    __syncthreads();                     // the shifts (and H(l, l-1) = 0) before the first rows change
+    // Bulge chase.  Bulge b starts EIG_GAP b steps after the first; its
+    // reflector acts on rows, then columns, k .. k+2 (k .. k+1 in its last
+    // step, where w2 = 0).  Rows of different bulges are disjoint, and so are
+    // their columns; row and column hi + 1 <= RMAX exist.  A step is two
+    // barriers, also for a wavefront that waits for its start or for the
+    // others' end, so every wavefront meets 2 (N - 1 + EIG_GAP (K - 1)).
+    const int b = wave & (EIG_K - 1);
+    auto idle = [](int steps) {
+      for (int i = 0; i < 2 * steps; ++i) __syncthreads();
+    };
+    if (b >= K) {
+      idle(N - 1 + EIG_GAP * (K - 1));
+    } else if (onH) {
+      idle(EIG_GAP * b);
+      const double h00 = Hm(l, l), h10 = Hm(l + 1, l);
+      double x = h00 * h00 + Hm(l, l + 1) * h10 - s * h00 + tt;
+      double y = h10 * (h00 + Hm(l + 1, l + 1) - s);
+      double z = h10 * Hm(l + 2, l + 1);
+      double* pc = H + t * LDH + l;                    // column t, rows k ..
+      double* pr = H + l * LDH + t;                    // row t, columns k ..
+      int bc = -1;                                     // bulge column: none in the first step
+      for (int k = l; k < hi; ++k) {
+        double c0 = pc[0], c1 = pc[1], c2 = pc[2];
+        const Reflector R = make_reflector(x, y, z);
+        if (VECS && t == 0) rf[b][(k - l) & 1] = R;
+        double d = -R.beta * __builtin_fma(R.w2, c2, __builtin_fma(R.w1, c1, R.w0 * c0));
+        const bool bulge = t == bc;                    // it becomes (alpha, 0, 0)
+        pc[0] = bulge ? R.alpha : __builtin_fma(d, R.w0, c0);
+        pc[1] = bulge ? 0.0 : __builtin_fma(d, R.w1, c1);
+        pc[2] = bulge ? 0.0 : __builtin_fma(d, R.w2, c2);
+        __syncthreads();
+        c0 = pr[0], c1 = pr[LDH], c2 = pr[2 * LDH];
+        d = -R.beta * __builtin_fma(R.w2, c2, __builtin_fma(R.w1, c1, R.w0 * c0));
+        c0 = __builtin_fma(d, R.w0, c0);
+        pr[0] = c0;
+        pr[LDH] = __builtin_fma(d, R.w1, c1);
+        pr[2 * LDH] = __builtin_fma(d, R.w2, c2);
+        // the next step's (x, y, z): the new H(k+1 .. k+3, k), zero past hi
+        x = readlane_d(c0, k + 1);
+        y = readlane_d(c0, (k + 2) & 63);
+        const long long zm = k + 3 <= hi ? -1ll : 0ll;
+        z = __longlong_as_double(__double_as_longlong(readlane_d(c0, (k + 3) & 63)) & zm);
+        bc = k;
+        ++pc;
+        pr += LDH;
+        __syncthreads();
+      }
+      idle(EIG_GAP * (K - 1 - b));
+    } else if (VECS) {
+      // Z's columns: the reflector is read after its step's first barrier
+      // and applied while the bulges go on (two slots per bulge: the one
+      // read here is written again two steps on, behind this wavefront's
+      // next arrival)
+      idle(EIG_GAP * b);
+      double* pz = Z + l * LDH + t;
+      for (int k = l; k < hi; ++k) {
+        __syncthreads();
+        const Reflector R = rf[b][(k - l) & 1];
+        const double c0 = pz[0], c1 = pz[LDH], c2 = pz[2 * LDH];
+        __syncthreads();
+        const double d = -R.beta * __builtin_fma(R.w2, c2, __builtin_fma(R.w1, c1, R.w0 * c0));
+        pz[0] = __builtin_fma(d, R.w0, c0);
+        pz[LDH] = __builtin_fma(d, R.w1, c1);
+        pz[2 * LDH] = __builtin_fma(d, R.w2, c2);
+        pz += LDH;
+      }
+      idle(EIG_GAP * (K - 1 - b));
     }
-    bulge_step<false, VECS>(H, Z, dum, n, l, hi, hi - 1, x, y, 0.0);
-    __syncthreads();
   }
   __syncthreads();
 
-  // 3. eigenvectors of the quasi-triangular T by back-substitution
+  // 3. eigenvectors of the quasi-triangular T by back-substitution (complex
+  //    arithmetic), eight lanes per eigenvalue: the sums over the known
+  //    entries are split over the lanes, which then all form the new ones
   const double smin = fmax(EPS * hn, 1e-300);
-  if (VECS && t < n && !sfail) {
-    const cplx lam = {wr[t], wi[t]};
-    for (int i = 0; i < n; ++i) {
-      Xr[t * LDH + i] = 0.0;
-      Xi[t * LDH + i] = 0.0;
-    }
+  const int ev = tid >> 3, el = tid & 7;
+  if (VECS && ev < n && !fail) {
+    double* xr = Xr + ev * LDH;
+    double* xi = Xi + ev * LDH;
+    const cplx lam = {wr[ev], wi[ev]};
+    for (int i = el; i < n; i += 8) xr[i] = xi[i] = 0.0;
+    wave_lds_fence();
     int start;
-    if (wi[t] == 0.0) {
-      Xr[t * LDH + t] = 1.0;
-      start = t - 1;
+    double mx;                            // running bound of the entries, for the rescaling test
+    if (wi[ev] == 0.0) {
+      if (el == 0) xr[ev] = 1.0;
+      start = ev - 1;
+      mx = 1.0;
     } else {
-      const int p = (wi[t] > 0.0) ? t : t - 1;  // block (p, p+1)
+      const int p = (wi[ev] > 0.0) ? ev : ev - 1;  // block (p, p+1)
       const int q = p + 1;
       const cplx a = {Hm(p, p), 0.0}, b = {Hm(p, q), 0.0};
       const cplx c = {Hm(q, p), 0.0}, d = {Hm(q, q), 0.0};
@@ -411,159 +464,148 @@ __device__ __forceinline__ void eig_body(DevState* st) {
         u1 = w1;
         u2 = w2;
       }
-      Xr[t * LDH + p] = u1.re;
-      Xi[t * LDH + p] = u1.im;
-      Xr[t * LDH + q] = u2.re;
-      Xi[t * LDH + q] = u2.im;
+      if (el == 0) {
+        xr[p] = u1.re;
+        xi[p] = u1.im;
+        xr[q] = u2.re;
+        xi[q] = u2.im;
+      }
       start = p - 1;
+      mx = fmax(fabs(u1.re) + fabs(u1.im), fabs(u2.re) + fabs(u2.im));
     }
-    // running bound of the computed entries, for the rescaling test
-    double mx = 0.0;
-    for (int j = start + 1; j < n; ++j) mx = fmax(mx, fabs(Xr[t * LDH + j]) + fabs(Xi[t * LDH + j]));
+    wave_lds_fence();
     int i = start;
     while (i >= 0) {
       const bool blk = i > 0 && Hm(i, i - 1) != 0.0;
       // s = sum_{j > i} H(row, j) x_j for the one or two rows of this block
-      // (H real: two real sums per row, two accumulators each)
+      // (H real: two real sums per row)
       const int i0 = blk ? i - 1 : i;
-      double s0r = 0.0, s0i = 0.0, s1r = 0.0, s1i = 0.0;   // row i0
-      double u0r = 0.0, u0i = 0.0, u1r = 0.0, u1i = 0.0;   // row i (block only)
-      int j = i + 1;
-      for (; j + 1 < n; j += 2) {
-        const double xr0 = Xr[t * LDH + j], xi0 = Xi[t * LDH + j];
-        const double xr1 = Xr[t * LDH + j + 1], xi1 = Xi[t * LDH + j + 1];
-        const double h0 = Hm(i0, j), h1 = Hm(i0, j + 1);
-        s0r = __builtin_fma(h0, xr0, s0r);
-        s0i = __builtin_fma(h0, xi0, s0i);
-        s1r = __builtin_fma(h1, xr1, s1r);
-        s1i = __builtin_fma(h1, xi1, s1i);
-        if (blk) {                               // this lane's block row
-          const double g0 = Hm(i, j), g1 = Hm(i, j + 1);
-          u0r = __builtin_fma(g0, xr0, u0r);
-          u0i = __builtin_fma(g0, xi0, u0i);
-          u1r = __builtin_fma(g1, xr1, u1r);
-          u1i = __builtin_fma(g1, xi1, u1i);
-        }
+      double sr = 0.0, si = 0.0;         // row i0
+      double ur = 0.0, ui = 0.0;         // row i (a 1 x 1 block reads the same row)
+#pragma unroll 2
+      for (int j = i + 1 + el; j < n; j += 8) {
+        const double vr = xr[j], vi = xi[j], h = Hm(i0, j), g = Hm(i, j);
+        sr = __builtin_fma(h, vr, sr);
+        si = __builtin_fma(h, vi, si);
+        ur = __builtin_fma(g, vr, ur);
+        ui = __builtin_fma(g, vi, ui);
       }
-      if (j < n) {
-        const double xr0 = Xr[t * LDH + j], xi0 = Xi[t * LDH + j];
-        const double h0 = Hm(i0, j);
-        s0r = __builtin_fma(h0, xr0, s0r);
-        s0i = __builtin_fma(h0, xi0, s0i);
-        if (blk) {
-          const double g0 = Hm(i, j);
-          u0r = __builtin_fma(g0, xr0, u0r);
-          u0i = __builtin_fma(g0, xi0, u0i);
-        }
-      }
+      sr = sum8(sr);
+      si = sum8(si);
+      ur = sum8(ur);
+      ui = sum8(ui);
       if (!blk) {
         cplx den = csub({Hm(i, i), 0.0}, lam);
         if (cabs2(den) < smin) den = {smin, 0.0};
-        const cplx xi = cdiv({-(s0r + s1r), -(s0i + s1i)}, den);
-        Xr[t * LDH + i] = xi.re;
-        Xi[t * LDH + i] = xi.im;
-        mx = fmax(mx, fabs(xi.re) + fabs(xi.im));
+        const cplx v = cdiv({-sr, -si}, den);
+        if (el == 0) {
+          xr[i] = v.re;
+          xi[i] = v.im;
+        }
+        mx = fmax(mx, fabs(v.re) + fabs(v.im));
         i -= 1;
       } else {
         const cplx m00 = csub({Hm(i0, i0), 0.0}, lam), m01 = {Hm(i0, i), 0.0};
         const cplx m10 = {Hm(i, i0), 0.0}, m11 = csub({Hm(i, i), 0.0}, lam);
         cplx det = csub(cmul(m00, m11), cmul(m01, m10));
         if (cabs2(det) < smin * smin) det = {smin * smin, 0.0};
-        const cplx r0 = {-(s0r + s1r), -(s0i + s1i)}, r1 = {-(u0r + u1r), -(u0i + u1i)};
+        const cplx r0 = {-sr, -si}, r1 = {-ur, -ui};
         const cplx x0 = cdiv(csub(cmul(r0, m11), cmul(m01, r1)), det);
         const cplx x1 = cdiv(csub(cmul(m00, r1), cmul(m10, r0)), det);
-        Xr[t * LDH + i0] = x0.re;
-        Xi[t * LDH + i0] = x0.im;
-        Xr[t * LDH + i] = x1.re;
-        Xi[t * LDH + i] = x1.im;
+        if (el == 0) {
+          xr[i0] = x0.re;
+          xi[i0] = x0.im;
+          xr[i] = x1.re;
+          xi[i] = x1.im;
+        }
         mx = fmax(mx, fmax(fabs(x0.re) + fabs(x0.im), fabs(x1.re) + fabs(x1.im)));
         i -= 2;
       }
+      wave_lds_fence();
       // rescale to keep the entries bounded
       if (mx > 1e100) {
         const double f = 1.0 / mx;
-        for (int jj = 0; jj < n; ++jj) {
-          Xr[t * LDH + jj] *= f;
-          Xi[t * LDH + jj] *= f;
+        for (int jj = el; jj < n; jj += 8) {
+          xr[jj] *= f;
+          xi[jj] *= f;
         }
         mx = 1.0;
+        wave_lds_fence();
       }
     }
   }
-  __syncthreads();
 
   // the eigenvalues at their rank in the output order; with vectors,
   // V = Z X normalised, at the same rank
-  if (t < n) hv[t] = hypot(wr[t], wi[t]);    // |lambda| (hv is free after the reduction)
+  if (tid < n) redb[0][tid] = hypot(wr[tid], wi[tid]);    // |lambda| (redb is free after the reduction)
   __syncthreads();
-  if (t < n && !sfail) {
-    const double ml = hv[t];
+  if (tid < n && !fail) {
+    const double ml = redb[0][tid];
     int rank = 0;
     for (int j = 0; j < n; ++j) {
-      const double mj = hv[j];
-      rank += (mj > ml) || (mj == ml && (wi[j] > wi[t] || (wi[j] == wi[t] && j < t)));
+      const double mj = redb[0][j];
+      rank += (mj > ml) || (mj == ml && (wi[j] > wi[tid] || (wi[j] == wi[tid] && j < tid)));
     }
-    st->lam_re[rank] = wr[t];
-    st->lam_im[rank] = wi[t];
-    if (VECS) {
-      double* __restrict__ vr = st->V_re + rank * RMAX;
-      double* __restrict__ vi = st->V_im + rank * RMAX;
-      // entries i0 .. i0+3 of Z X[:, t]: one load of x_j serves four rows of
-      // Z (rows past n read row 0 and are not used)
-      auto zx4 = [&](int i0, double (&ar)[4], double (&ai)[4]) {
-        int ir[4];
+    st->lam_re[rank] = ldexp(wr[tid], ex);
+    st->lam_im[rank] = ldexp(wi[tid], ex);
+    if (VECS) pos[tid] = rank;
+  }
+  if (VECS) {
+    __syncthreads();
+    if (ev < n && !fail) {
+      // lane el of an eigenvalue's eight holds the entries el, el + 8, ...
+      // of Z X[:, ev] (Z is zero past n rows)
+      constexpr int NE = RMAX / 8;
+      double ar[NE], ai[NE];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          ar[u] = 0.0;
-          ai[u] = 0.0;
-          ir[u] = i0 + u < n ? i0 + u : 0;
-        }
-        for (int j = 0; j < n; ++j) {
-          const double xr = Xr[t * LDH + j], xi = Xi[t * LDH + j];
+      for (int u = 0; u < NE; ++u) ar[u] = ai[u] = 0.0;
+      for (int j = 0; j < n; ++j) {
+        const double vr = Xr[ev * LDH + j], vi = Xi[ev * LDH + j];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const double z = Zm(ir[u], j);
-            ar[u] = __builtin_fma(z, xr, ar[u]);
-            ai[u] = __builtin_fma(z, xi, ai[u]);
-          }
+        for (int u = 0; u < NE; ++u) {
+          const double z = Zm(el + 8 * u, j);
+          ar[u] = __builtin_fma(z, vr, ar[u]);
+          ai[u] = __builtin_fma(z, vi, ai[u]);
         }
-      };
-      // first pass: the norm and the largest-modulus entry; the second forms
-      // the entries again (bit for bit) and writes them normalised
+      }
+      // unit norm, largest-modulus entry (the first of equal ones) real and
+      // positive: multiply by conj(v_ib) / (|v_ib| ||v||)
       double nrm2 = 0.0, best = -1.0, vbr = 0.0, vbi = 0.0;
       int ib = 0;
-      for (int i0 = 0; i0 < n; i0 += 4) {
-        double ar[4], ai[4];
-        zx4(i0, ar, ai);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (i0 + u < n) {
-            const double m2 = ar[u] * ar[u] + ai[u] * ai[u];
-            nrm2 += m2;
-            if (m2 > best) {
-              best = m2;
-              ib = i0 + u;
-              vbr = ar[u];
-              vbi = ai[u];
-            }
+      for (int u = 0; u < NE; ++u) {
+        const double m2 = ar[u] * ar[u] + ai[u] * ai[u];
+        if (el + 8 * u < n) {
+          nrm2 += m2;
+          if (m2 > best) {
+            best = m2;
+            ib = el + 8 * u;
+            vbr = ar[u];
+            vbi = ai[u];
           }
         }
       }
-      // unit norm, largest-modulus entry real and positive: multiply by
-      // conj(v_ib) / (|v_ib| ||v||)
+      nrm2 = sum8(nrm2);
+#pragma unroll
+      for (int o = 4; o > 0; o >>= 1) {
+        const double ob = __shfl_xor(best, o, 8), orr = __shfl_xor(vbr, o, 8), oi = __shfl_xor(vbi, o, 8);
+        const int oib = __shfl_xor(ib, o, 8);
+        const bool take = ob > best || (ob == best && oib < ib);
+        best = take ? ob : best;
+        vbr = take ? orr : vbr;
+        vbi = take ? oi : vbi;
+        ib = take ? oib : ib;
+      }
       const double m = sqrt(best), f = 1.0 / sqrt(nrm2);
       const double pr = vbr / m * f, pi = -vbi / m * f;
-                                               // V[:, rank] = (Z X[:, t]) (pr + i pi)
-      for (int i0 = 0; i0 < n; i0 += 4) {
-        double ar[4], ai[4];
-        zx4(i0, ar, ai);
+      double* __restrict__ vr = st->V_re + pos[ev] * RMAX;
+      double* __restrict__ vi = st->V_im + pos[ev] * RMAX;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = i0 + u;
-          if (i < n) {
-            vr[i] = ar[u] * pr - ai[u] * pi;
-            vi[i] = i == ib ? 0.0 : ar[u] * pi + ai[u] * pr;
-          }
+      for (int u = 0; u < NE; ++u) {
+        const int i = el + 8 * u;
+        if (i < n) {
+          vr[i] = ar[u] * pr - ai[u] * pi;
+          vi[i] = i == ib ? 0.0 : ar[u] * pi + ai[u] * pr;
         }
       }
     }
@@ -571,9 +613,9 @@ __device__ __forceinline__ void eig_body(DevState* st) {
   __threadfence();
   __syncthreads();
 
-  if (t == 0) {
-    st->eig_status = sfail;
-    if (sfail) latch_status(st, ST_NOCONV);
+  if (tid == 0) {
+    st->eig_status = fail;
+    if (fail) latch_status(st, ST_NOCONV);
     st->eig_valid = VECS ? 2 : 1;
   }
 }
@@ -798,11 +840,11 @@ __global__ __launch_bounds__(256) void k_basis_coef(DevState* st) {
 }
 
 template <bool VECS>
-__global__ __launch_bounds__(64) void k_eig(DevState* st) { eig_body<VECS>(st); }
+__global__ __launch_bounds__(eig_threads<VECS>()) void k_eig(DevState* st) { eig_body<VECS>(st); }
 
 hipError_t launch_eig(DevState* st, bool vectors, hipStream_t s) {
-  if (vectors) hipLaunchKernelGGL(k_eig<true>, dim3(1), dim3(64), 0, s, st);
-  else hipLaunchKernelGGL(k_eig<false>, dim3(1), dim3(64), 0, s, st);
+  if (vectors) hipLaunchKernelGGL(k_eig<true>, dim3(1), dim3(eig_threads<true>()), 0, s, st);
+  else hipLaunchKernelGGL(k_eig<false>, dim3(1), dim3(eig_threads<false>()), 0, s, st);
   return hipGetLastError();
 }
 
