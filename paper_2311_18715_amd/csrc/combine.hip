@@ -7,31 +7,45 @@
 // write per predicted state).
 //
 // As a product it is Out (K x n) = Coef (K x m) S^T (m x n) with a short
-// contraction (m <= 72): 2 K n m flops against K n output writes.  For
-// FP64 states the writes bound it (a 500-state read-out at n = 160,000 moves
-// 889 MB, 178 us at the device-copy rate, against 98 us of FP64
-// matrix-core time); for FP32 states and wide bases the two are close.  It
-// runs on the FP64 matrix cores (16x16x4): a wavefront takes 16 rows of one tile in
-// the streaming pass's operand layout (lane l holds row l%16 of stored
+// contraction (m <= 72): 2 K n m flops against K n output writes.  It runs
+// on the FP64 matrix cores (16x16x4): a wavefront takes 16 rows of one tile
+// in the streaming pass's operand layout (lane l holds row l%16 of stored
 // columns 4 kk + l/16, so one column of the unit is a 128-byte line for
-// FP64) and multiplies them by 16-step blocks of coefficients staged in LDS
+// FP64) and multiplies them by 16-state blocks of coefficients staged in LDS
 // in the operand layout; lane l then holds states 4 v + l/16 of the block
-// at row l%16, so 16 lanes write 16 consecutive rows of one state (streaming
-// stores: the states are not read again here).  The
+// at row l%16, so 16 lanes write 16 consecutive rows of one state.  The
 // stored values convert exactly to FP64, the coefficients are FP64 and so
 // are the sums; the output is rounded once, to its type.  A workgroup covers
-// a contiguous share of the rows (about CB_RPW or more: the grid holds no more
-// workgroups than the GPU runs at once) and 16 NS states; the stored
-// columns are read once per 16 NS states.  FP32 states from FP32 or BF16
-// stored columns take k_combine32 instead (FP32 matrix cores, 128-byte
-// stores); a few states (K <= 4) take k_combine_rows.
+// a contiguous share of the rows and 16 NS states; the stored columns are
+// read once per 16 NS states.  FP32 states from FP32 or BF16 stored columns
+// take the FP32 matrix cores instead (128-byte stores); a few states
+// (K <= 4) take one row or a few per lane.
+//
+// The writes bound it, and how they are made decides their rate.  A state's
+// rows start at any multiple of the element size, so a wavefront's piece of
+// a state is usually not whole 128-byte lines.  Streaming (nontemporal)
+// stores send such pieces to memory as partial lines: 100 states of
+// n = 585,732 FP32 rows as bare stores, 1.7 TB/s against 5.4 TB/s with
+// ordinary stores, which merge neighbouring pieces in L2; only where every
+// state starts on a line do they cost nothing (and save a little: 500 FP64
+// states at n = 160,000, 214 against 228 us).  So streaming stores are used
+// only there.  Pieces merge when neighbours are written
+// soon after each other, so few wavefronts write at a time: one workgroup
+// per CU in all, each on a contiguous share of the rows (100 FP32 states,
+// n = 585,732: 112 us with one, 126 with two, 140 with three).  The
+// store addresses step by one 64-bit add each from an opaque start: left
+// to itself the compiler held every state's address in registers (230
+// registers, two waves per SIMD, spills with the next unit's loads in flight).
+// Before and after (streaming stores everywhere, two workgroups per CU):
+// 100 FP32 states, n = 585,732, 178 -> 115 us; FP64, 100 states of n = 160,001
+// 115 -> 56 us, 500 of them 541 -> 294 us; 500 states of n = 160,000 (whole
+// lines) 167 us, as before.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <type_traits>
 #include <map>
 #include <mutex>
-#include <utility>
 
 #include "odmd_internal.h"
 #include "pass.h"
@@ -45,79 +59,90 @@ __device__ __forceinline__ float to_float_value(float v) { return v; }
 __device__ __forceinline__ float to_float_value(bf16 v) { return __uint_as_float((uint32_t)v.bits << 16); }
 
 constexpr int CB_THREADS = 256;          // four wavefronts
-constexpr int CB_RPW = 512;              // rows per workgroup, at least
 
-// NS 16-state blocks per workgroup (the host picks NS from the number of
-// states, so that a short rollout computes no more than 16 states in vain)
-template <typename TS, typename TO, int RB, int NS>
-__global__ __launch_bounds__(CB_THREADS) void k_combine(CombineArgs c) {
+// Wave-uniform base address of a unit's rows (scalar registers; each lane
+// adds a constant 32-bit offset)
+__device__ __forceinline__ gbytes uniform_base(const void* p) {
+  const uint64_t b = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+  return (gbytes)(((uint64_t)hi << 32) | lo);
+}
+
+// Element at a byte address of global memory, by a streaming or an ordinary store
+template <bool NT, typename TO>
+__device__ __forceinline__ void put(uint64_t at, TO v) {
+  typedef __attribute__((address_space(1))) TO* gptr;
+  if constexpr (NT) __builtin_nontemporal_store(v, (gptr)at);
+  else *(gptr)at = v;
+}
+
+// Workgroup bx of gx (a contiguous share of the 16-row units), states 16 NS by
+// .. 16 NS (by + 1) - 1.  smem: combine_lds<RB, NS>() doubles.
+template <int RB, int NS>
+constexpr int combine_lds() { return NS * (RB / 4) * 64; }
+template <typename TS, typename TO, int RB, int NS, bool NT>
+__device__ __forceinline__ void combine_body(const CombineArgs& c, const int bx, const int gx, const int by,
+                                             double* sC) {
   typedef Storage<TS> SC;
   constexpr int KK = RB / 4;                 // k-steps over the stored columns
   constexpr int NW = CB_THREADS / 64;
+  typedef typename std::conditional<sizeof(TS) == 8, uint64_t, uint32_t>::type raw_t;
   const DevState* __restrict__ st = c.st;
   const int m = st->m;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int q = lane >> 4, l16 = lane & 15;
-  const int k0 = blockIdx.y * (16 * NS);
+  const int k0 = by * (16 * NS);
 
-  // coefficients of the workgroup's states in the A-operand layout:
-  // sC[s][kk][lane] = coef(state k0 + 16 s + lane%16, column 4 kk + lane/16)
-  __shared__ double sC[NS][KK][64];
-  for (int idx = threadIdx.x; idx < NS * KK * 64; idx += CB_THREADS) {
-    const int ln = idx & 63, kk = (idx >> 6) % KK, s = (idx >> 6) / KK;
+  // coefficients of the workgroup's states in the A-operand layout: entry
+  // [kk][s][lane] = coef(state k0 + 16 s + lane%16, column 4 kk + lane/16)
+  for (int idx = threadIdx.x; idx < combine_lds<RB, NS>(); idx += CB_THREADS) {
+    const int ln = idx & 63, s = (idx >> 6) % NS, kk = (idx >> 6) / NS;
     const int k = k0 + 16 * s + (ln & 15), col = 4 * kk + (ln >> 4);
-    sC[s][kk][ln] = (k < c.K && col < m) ? st->coefA[k * CMAX + col] : 0.0;
+    sC[idx] = (k < c.K && col < m) ? st->coefA[k * CMAX + col] : 0.0;
   }
 
-  const TS* __restrict__ Us = static_cast<const TS*>(c.Us);
-  TO* __restrict__ out = static_cast<TO*>(c.out);
-  // the workgroup's rows: a contiguous share of the 16-row units (the
-  // launch sizes the grid to the workgroups the GPU holds at once, so the
-  // last round of workgroups does not run the chip part empty)
   const int64_t units = (c.n + 15) / 16;
-  const int64_t ub = (int64_t)blockIdx.x * units / gridDim.x;
-  const int64_t ue = (int64_t)(blockIdx.x + 1) * units / gridDim.x;
-  const int64_t r0 = 16 * ub;
-  const int nunit = (int)(ue - ub);
-  const int kmax = (m + 3) / 4;              // live k-steps (uniform)
-  // the unit's stored values stay in their storage type until used; the next
-  // unit's loads are in flight while the current one is multiplied
-  auto load = [&](int u, TS (&A)[KK]) {
-    const int64_t row0 = r0 + 16 * u;        // 16-row units never straddle a tile
-    const TS* __restrict__ T = Us + (row0 >> 6) * (int64_t)c.ct * 64 + (row0 & 63);
+  const int64_t ub = (int64_t)bx * units / gx, ue = (int64_t)(bx + 1) * units / gx;
+  const uint32_t loff = (uint32_t)((q * 64 + l16) * sizeof(TS));
+  // 16-row units never straddle a tile; a k-step past the m live columns
+  // re-reads the first (a cache hit; its coefficients are zero and stored
+  // values are finite)
+  auto load = [&](int64_t u, raw_t (&A)[KK]) {
+    const gbytes base = uniform_base(static_cast<const TS*>(c.Us) + (u >> 2) * (int64_t)c.ct * 64 + 16 * (u & 3));
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)
-      if (kk < kmax) A[kk] = T[(4 * kk + q) * 64 + l16];
+      A[kk] = (raw_t)SC::row(base + (4 * kk < m ? kk : 0) * 256 * (int)sizeof(TS) + loff);
   };
-  TS A[KK], An[KK];
-  int u = wave;
-  if (u < nunit) load(u, A);
+  raw_t A[KK], An[KK];                       // the next unit's loads are in flight during the products
+  int64_t u = ub + wave;
+  load(u < ue ? u : ub, A);
   __syncthreads();
-  for (; u < nunit; u += NW) {
-    if (u + NW < nunit) load(u + NW, An);    // uniform
+  const int full = min(NS, (c.K - k0) / 16); // blocks with 16 states
+  for (; u < ue; u += NW) {
+    load(u + NW < ue ? u + NW : u, An);
+    // (opaque: the coefficients are read again for every unit, not held)
+    int at = lane;
+    asm volatile("" : "+v"(at));
     d4_t d[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) d[s] = d4_t{0.0, 0.0, 0.0, 0.0};
     // the NS accumulator chains are independent: k-steps outermost
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      if (kk < kmax) {                       // uniform
-        const double a = SC::to_double(A[kk]);
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-          d[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(sC[s][kk][lane], a, d[s], 0, 0, 0);
-      }
-    }
-    // the states are written once and not read again here: streaming stores
-    const int64_t row = r0 + 16 * u + l16;
-    if (row < c.n) {
+      const double a = SC::to_double(SC::elem(A[kk], 0));
 #pragma unroll
       for (int s = 0; s < NS; ++s)
+        d[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(sC[(kk * NS + s) * 64 + at], a, d[s], 0, 0, 0);
+    }
+    const int64_t row = 16 * u + l16;
+    if (row < c.n) {
+      uint64_t p = reinterpret_cast<uint64_t>(static_cast<TO*>(c.out) + (int64_t)(k0 + q) * c.ldo + row);
+      const uint64_t step = (uint64_t)c.ldo * 4 * sizeof(TO);
+      asm volatile("" : "+v"(p));
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int k = k0 + 16 * s + 4 * v + q;
-          if (k < c.K) __builtin_nontemporal_store((TO)d[s][v], out + (int64_t)k * c.ldo + row);
-        }
+      for (int e = 0; e < 4 * NS; ++e, p += step)
+        if (e < 4 * full || k0 + 4 * e + q < c.K) put<NT>(p, (TO)d[e / 4][e % 4]);
     }
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) A[kk] = An[kk];
@@ -126,7 +151,7 @@ __global__ __launch_bounds__(CB_THREADS) void k_combine(CombineArgs c) {
 
 // FP32 states from FP32 or BF16 stored columns: the same product on the
 // FP32 matrix cores (32x32x2, twice the FP64 rate), which also writes
-// whole 128-byte lines: a wavefront takes 32 consecutive rows of one tile
+// 128-byte pieces: a wavefront takes 32 consecutive rows of one tile
 // (lane l supplies row l%32 of stored column 2 kk + l/32; 32 lanes read a
 // 128-byte line of a column), and register r of lane l holds state
 // 8 (r/4) + 4 (l/32) + r%4 of a 32-state block at row l%32, so 32 lanes
@@ -135,46 +160,49 @@ __global__ __launch_bounds__(CB_THREADS) void k_combine(CombineArgs c) {
 // m FP32 roundings per state against one for the FP64 path: the output is
 // FP32 either way).  NS 32-state blocks per workgroup; with one block the
 // k-steps alternate between two accumulators, so that two product chains
-// are in flight.
-template <typename TS, int RB, int NS>
-__global__ __launch_bounds__(CB_THREADS, 2) void k_combine32(CombineArgs c) {
+// are in flight.  smem: combine32_lds<RB, NS>() floats.
+template <int RB, int NS>
+constexpr int combine32_lds() { return NS * (RB / 2) * 64; }
+template <typename TS, int RB, int NS, bool NT>
+__device__ __forceinline__ void combine32_body(const CombineArgs& c, const int bx, const int gx, const int by,
+                                               float* sC) {
+  typedef Storage<TS> SC;
   constexpr int KK = RB / 2;                 // k-steps over the stored columns
   constexpr int NA = NS == 1 ? 2 : 1;        // accumulators per block
   constexpr int NW = CB_THREADS / 64;
   typedef float f16v __attribute__((ext_vector_type(16)));
+  typedef typename std::conditional<sizeof(TS) == 4, uint32_t, uint16_t>::type raw_t;
   const DevState* __restrict__ st = c.st;
   const int m = st->m;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int h = lane >> 5, l32 = lane & 31;
-  const int k0 = blockIdx.y * (32 * NS);
+  const int k0 = by * (32 * NS);
 
-  // sC[s][kk][lane] = coef(state k0 + 32 s + lane%32, column 2 kk + lane/32)
-  __shared__ float sC[NS][KK][64];
-  for (int idx = threadIdx.x; idx < NS * KK * 64; idx += CB_THREADS) {
-    const int ln = idx & 63, kk = (idx >> 6) % KK, s = (idx >> 6) / KK;
+  // entry [kk][s][lane] = coef(state k0 + 32 s + lane%32, column 2 kk + lane/32)
+  for (int idx = threadIdx.x; idx < combine32_lds<RB, NS>(); idx += CB_THREADS) {
+    const int ln = idx & 63, s = (idx >> 6) % NS, kk = (idx >> 6) / NS;
     const int k = k0 + 32 * s + (ln & 31), col = 2 * kk + (ln >> 5);
-    sC[s][kk][ln] = (k < c.K && col < m) ? (float)st->coefA[k * CMAX + col] : 0.f;
+    sC[idx] = (k < c.K && col < m) ? (float)st->coefA[k * CMAX + col] : 0.f;
   }
 
-  const TS* __restrict__ Us = static_cast<const TS*>(c.Us);
-  float* __restrict__ out = static_cast<float*>(c.out);
   const int64_t units = (c.n + 31) / 32;     // 32-row units (two per 64-row tile)
-  const int64_t ub = (int64_t)blockIdx.x * units / gridDim.x;
-  const int64_t ue = (int64_t)(blockIdx.x + 1) * units / gridDim.x;
-  const int64_t r0 = 32 * ub;
-  const int nunit = (int)(ue - ub);
-  const int kmax = (m + 1) / 2;              // live k-steps (uniform)
-  auto load = [&](int u, float (&B)[KK]) {
-    const int64_t row0 = r0 + 32 * u;
-    const TS* __restrict__ T = Us + (row0 >> 6) * (int64_t)c.ct * 64 + (row0 & 63);
+  const int64_t ub = (int64_t)bx * units / gx, ue = (int64_t)(bx + 1) * units / gx;
+  const uint32_t loff = (uint32_t)((h * 64 + l32) * sizeof(TS));
+  auto load = [&](int64_t u, raw_t (&B)[KK]) {
+    const gbytes base = uniform_base(static_cast<const TS*>(c.Us) + (u >> 1) * (int64_t)c.ct * 64 + 32 * (u & 1));
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)
-      if (kk < kmax) B[kk] = to_float_value(T[(2 * kk + h) * 64 + l32]);
+      B[kk] = (raw_t)SC::row(base + (2 * kk < m ? kk : 0) * 128 * (int)sizeof(TS) + loff);
   };
-  float B[KK];
+  raw_t B[KK], Bn[KK];
+  int64_t u = ub + wave;
+  load(u < ue ? u : ub, B);
   __syncthreads();
-  for (int u = wave; u < nunit; u += NW) {
-    load(u, B);                              // two waves per SIMD hide the loads
+  const int full = min(NS, (c.K - k0) / 32); // blocks with 32 states
+  for (; u < ue; u += NW) {
+    load(u + NW < ue ? u + NW : u, Bn);
+    int at = lane;
+    asm volatile("" : "+v"(at));
     f16v d[NS][NA];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -182,25 +210,24 @@ __global__ __launch_bounds__(CB_THREADS, 2) void k_combine32(CombineArgs c) {
       for (int a = 0; a < NA; ++a) d[s][a] = f16v{};
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      if (kk < kmax) {                       // uniform
+      const float b = to_float_value(SC::elem(B[kk], 0));
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
-          d[s][kk % NA] = __builtin_amdgcn_mfma_f32_32x32x2f32(sC[s][kk][lane], B[kk], d[s][kk % NA], 0, 0, 0);
-      }
+      for (int s = 0; s < NS; ++s)
+        d[s][kk % NA] = __builtin_amdgcn_mfma_f32_32x32x2f32(sC[(kk * NS + s) * 64 + at], b, d[s][kk % NA], 0, 0, 0);
     }
-    const int64_t row = r0 + 32 * u + l32;
+    if (NA == 2) d[0][0] += d[0][NA - 1];
+    const int64_t row = 32 * u + l32;
     if (row < c.n) {
+      uint64_t p = reinterpret_cast<uint64_t>(static_cast<float*>(c.out) + (int64_t)(k0 + 4 * h) * c.ldo + row);
+      const uint64_t step = (uint64_t)c.ldo * sizeof(float);
+      asm volatile("" : "+v"(p));
+      // register r of a block: state 8 (r/4) + r%4 (+ 4 h)
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        f16v e = d[s][0];
-        if (NA == 2) e += d[s][NA - 1];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int k = k0 + 32 * s + 8 * (r >> 2) + 4 * h + (r & 3);
-          if (k < c.K) __builtin_nontemporal_store(e[r], out + (int64_t)k * c.ldo + row);
-        }
-      }
+      for (int e = 0; e < 16 * NS; ++e, p += e % 4 ? step : 5 * step)
+        if (e < 16 * full || k0 + 8 * (e / 4) + e % 4 + 4 * h < c.K) put<NT>(p, d[e / 16][0][e % 16]);
     }
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) B[kk] = Bn[kk];
   }
 }
 
@@ -257,54 +284,88 @@ __device__ __forceinline__ void combine_rows_body(const CombineArgs& c, const in
   }
 }
 
-template <typename TS, typename TO, int RB>
-__global__ __launch_bounds__(256) void k_combine_rows(CombineArgs c) {
-  combine_rows_body<TS, TO, RB>(c, blockIdx.x);
-}
-
-// Workgroups of kernel f the GPU holds at once (its occupancy per CU times
-// the CUs of the current device), cached per kernel and device.
-static int resident_blocks(const void* f) {
-  static std::mutex mu;
-  static std::map<std::pair<const void*, int>, int> cache;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  std::lock_guard<std::mutex> lk(mu);
-  auto it = cache.find({f, dev});
-  if (it != cache.end()) return it->second;
-  int per_cu = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, CB_THREADS, 0) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
-    (void)hipGetLastError();
-    return 0;
+enum { KIND_ROWS, KIND_FP64, KIND_FP32 };
+template <int KIND, typename TS, typename TO, int RB, int NS, bool NT>
+__device__ __forceinline__ void combine_block(const CombineArgs& c, int bx, int gx, int by) {
+  if constexpr (KIND == KIND_ROWS) {
+    combine_rows_body<TS, TO, RB>(c, bx);
+  } else if constexpr (KIND == KIND_FP64) {
+    __shared__ double smem[combine_lds<RB, NS>()];
+    combine_body<TS, TO, RB, NS, NT>(c, bx, gx, by, smem);
+  } else {
+    __shared__ float smem[combine32_lds<RB, NS>()];
+    combine32_body<TS, RB, NS, NT>(c, bx, gx, by, smem);
   }
-  return cache[{f, dev}] = per_cu * cus;
 }
 
-// Row workgroups: one per CB_RPW rows at most, and no more than the GPU holds
-// at once together with the launch's other state blocks (then every
-// workgroup gets a larger, equal share of the rows).  Workgroups go to the
+template <int KIND, typename TS, typename TO, int RB, int NS, bool NT>
+__global__ __launch_bounds__(CB_THREADS) void k_combine(CombineArgs c) {
+  combine_block<KIND, TS, TO, RB, NS, NT>(c, blockIdx.x, gridDim.x, blockIdx.y);
+}
+
+// Read-out class of a launch: the kernel and its states per workgroup.  A
+// few states are read bound (rows); FP32 states of FP32 or BF16 columns go to
+// the FP32 matrix cores in up to four 32-state blocks, the rest to the FP64
+// ones in one, two, four or eight 16-state blocks: no more than a block of
+// states is computed in vain, and a workgroup's accumulators fit its
+// registers.  (More blocks per workgroup: more independent accumulator
+// chains and fewer re-reads of the stored columns.)
+struct CombineClass { int kind, ns, states; };   // states: per workgroup
+static CombineClass combine_class(int basis, int out_f32, int K) {
+  if (K <= CR_KMAX) return {KIND_ROWS, 1, K};
+  if (out_f32 && basis != 0) {
+    const int ns = std::min(4, (K + 31) / 32);
+    return {KIND_FP32, ns, 32 * ns};
+  }
+  const int ns = K <= 16 ? 1 : (K <= 32 ? 2 : (K <= 64 ? 4 : 8));
+  return {KIND_FP64, ns, 16 * ns};
+}
+
+static int cu_count() {
+  static std::mutex mu;
+  static std::map<int, int> cache;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  std::lock_guard<std::mutex> lk(mu);
+  auto it = cache.find(dev);
+  if (it != cache.end()) return it->second;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+    (void)hipGetLastError();
+    return 256;
+  }
+  return cache[dev] = cus;
+}
+
+// Grid of one read-out.  Rows: one thread per 8 bytes of a column.  Else one
+// workgroup per CU in all (two with streaming stores; see the top of the
+// file), shared by the launch's state blocks, with a unit per wavefront at least.  Workgroups go to the
 // eight XCDs in turn by linear index x + g y; with g a multiple of 8 the
 // state blocks of one row share run on the same XCD and read its stored
-// columns through one L2 (with g = 170 and three state blocks, the columns
-// were fetched three times).
-template <typename K>
-static dim3 combine_grid(K f, const CombineArgs& c, int NS) {
-  const unsigned ys = (unsigned)((c.K + 16 * NS - 1) / (16 * NS));
-  int64_t g = (c.n + CB_RPW - 1) / CB_RPW;
-  const int res = resident_blocks(reinterpret_cast<const void*>(f));
-  if (res > 0) g = std::min<int64_t>(g, std::max<int64_t>(1, res / (int64_t)ys));
+// columns through one L2.
+static dim3 combine_grid(const CombineArgs& c, const CombineClass& k, int basis, bool nt) {
+  if (k.kind == KIND_ROWS) {
+    const int64_t rows = CB_THREADS * (basis == 0 ? 1 : (basis == 1 ? 2 : 4));
+    return dim3((unsigned)((c.n + rows - 1) / rows), 1);
+  }
+  const int ur = (k.kind == KIND_FP32 ? 32 : 16) * (CB_THREADS / 64);
+  const unsigned ys = (unsigned)((c.K + k.states - 1) / k.states);
+  int64_t g = std::min<int64_t>((c.n + ur - 1) / ur, std::max<int64_t>(1, (nt ? 2 : 1) * cu_count() / (int64_t)ys));
   if (ys > 1 && g > 8) g = g / 8 * 8;
   return dim3((unsigned)g, ys);
 }
 
-template <typename TS, typename TO, int NS>
-static hipError_t launch_ns(const CombineArgs& c, int rb, hipStream_t s) {
-  const dim3 block(CB_THREADS);
+// every state starts on a 128-byte line
+static bool whole_lines(const CombineArgs& c, int out_f32) {
+  const int64_t es = out_f32 ? 4 : 8;
+  return reinterpret_cast<uintptr_t>(c.out) % 128 == 0 && (c.K == 1 || c.ldo * es % 128 == 0);
+}
+
+template <int KIND, typename TS, typename TO, int NS, bool NT>
+static hipError_t launch_rb(const CombineArgs& c, const dim3& grid, int rb, hipStream_t s) {
   switch (rb) {
 #define ODMD_CASE(RB) \
-  case RB: hipLaunchKernelGGL((k_combine<TS, TO, RB, NS>), combine_grid(k_combine<TS, TO, RB, NS>, c, NS), \
-                              block, 0, s, c); break;
+  case RB: hipLaunchKernelGGL((k_combine<KIND, TS, TO, RB, NS, NT>), grid, dim3(CB_THREADS), 0, s, c); break;
     ODMD_CASE(8) ODMD_CASE(16) ODMD_CASE(24) ODMD_CASE(32) ODMD_CASE(40) ODMD_CASE(48)
     ODMD_CASE(56) ODMD_CASE(64) ODMD_CASE(72)
 #undef ODMD_CASE
@@ -313,60 +374,36 @@ static hipError_t launch_ns(const CombineArgs& c, int rb, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename TS, int NS>
-static hipError_t launch_ns32(const CombineArgs& c, int rb, hipStream_t s) {
-  const dim3 block(CB_THREADS);
-  switch (rb) {
-#define ODMD_CASE(RB) \
-  case RB: hipLaunchKernelGGL((k_combine32<TS, RB, NS>), combine_grid(k_combine32<TS, RB, NS>, c, 2 * NS), \
-                              block, 0, s, c); break;
-    ODMD_CASE(8) ODMD_CASE(16) ODMD_CASE(24) ODMD_CASE(32) ODMD_CASE(40) ODMD_CASE(48)
-    ODMD_CASE(56) ODMD_CASE(64) ODMD_CASE(72)
-#undef ODMD_CASE
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-template <typename TS, typename TO>
-static hipError_t launch_rows(const CombineArgs& c, int rb, hipStream_t s) {
-  const int64_t rows = 256 * (8 / (int)sizeof(TS));   // rows per workgroup
-  const dim3 grid((unsigned)((c.n + rows - 1) / rows)), block(256);
-  switch (rb) {
-#define ODMD_CASE(RB) \
-  case RB: hipLaunchKernelGGL((k_combine_rows<TS, TO, RB>), grid, block, 0, s, c); break;
-    ODMD_CASE(8) ODMD_CASE(16) ODMD_CASE(24) ODMD_CASE(32) ODMD_CASE(40) ODMD_CASE(48)
-    ODMD_CASE(56) ODMD_CASE(64) ODMD_CASE(72)
-#undef ODMD_CASE
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-template <typename TS, typename TO>
-static hipError_t launch_t(const CombineArgs& c, int rb, hipStream_t s) {
-  if (c.K <= CR_KMAX) return launch_rows<TS, TO>(c, rb, s);
+template <typename TS, typename TO, bool NT>
+static hipError_t launch_t(const CombineArgs& c, int basis, int out_f32, int rb, hipStream_t s) {
+  const CombineClass k = combine_class(basis, out_f32, c.K);
+  const dim3 grid = combine_grid(c, k, basis, NT);
+  if (k.kind == KIND_ROWS) return launch_rb<KIND_ROWS, TS, TO, 1, false>(c, grid, rb, s);
   if constexpr (std::is_same<TO, float>::value && !std::is_same<TS, double>::value) {
-    if (c.K <= 32) return launch_ns32<TS, 1>(c, rb, s);
-    if (c.K <= 64) return launch_ns32<TS, 2>(c, rb, s);
-    return launch_ns32<TS, 4>(c, rb, s);
+    switch (k.ns) {
+      case 1: return launch_rb<KIND_FP32, TS, TO, 1, NT>(c, grid, rb, s);
+      case 2: return launch_rb<KIND_FP32, TS, TO, 2, NT>(c, grid, rb, s);
+      case 3: return launch_rb<KIND_FP32, TS, TO, 3, NT>(c, grid, rb, s);
+      default: return launch_rb<KIND_FP32, TS, TO, 4, NT>(c, grid, rb, s);
+    }
+  } else {
+    switch (k.ns) {
+      case 1: return launch_rb<KIND_FP64, TS, TO, 1, NT>(c, grid, rb, s);
+      case 2: return launch_rb<KIND_FP64, TS, TO, 2, NT>(c, grid, rb, s);
+      case 4: return launch_rb<KIND_FP64, TS, TO, 4, NT>(c, grid, rb, s);
+      default: return launch_rb<KIND_FP64, TS, TO, 8, NT>(c, grid, rb, s);
+    }
   }
-  // more 16-state blocks per workgroup: more independent accumulator
-  // chains per wave (the FP64 matrix-core chains are latency-bound: 500
-  // states at n = 160,000 and 56 columns took 182 us of matrix-core time
-  // with eight blocks against 237 us with four) and fewer re-reads of the
-  // stored columns, at the price of LDS (eight blocks of 72 columns: 72 KB)
-  if (c.K <= 16) return launch_ns<TS, TO, 1>(c, rb, s);
-  if (c.K <= 32) return launch_ns<TS, TO, 2>(c, rb, s);
-  if (c.K <= 64) return launch_ns<TS, TO, 4>(c, rb, s);
-  return launch_ns<TS, TO, 8>(c, rb, s);
 }
 
 hipError_t launch_combine(const CombineArgs& c, int basis, int out_f32, int rb, hipStream_t s) {
-  switch (basis) {
-    case 0: return out_f32 ? launch_t<double, float>(c, rb, s) : launch_t<double, double>(c, rb, s);
-    case 1: return out_f32 ? launch_t<float, float>(c, rb, s) : launch_t<float, double>(c, rb, s);
-    case 2: return out_f32 ? launch_t<bf16, float>(c, rb, s) : launch_t<bf16, double>(c, rb, s);
+  const bool nt = whole_lines(c, out_f32);
+  switch (2 * basis + (out_f32 ? 1 : 0)) {   // (an FP64 basis has FP64 states)
+    case 0: return nt ? launch_t<double, double, true>(c, basis, 0, rb, s) : launch_t<double, double, false>(c, basis, 0, rb, s);
+    case 2: return nt ? launch_t<float, double, true>(c, basis, 0, rb, s) : launch_t<float, double, false>(c, basis, 0, rb, s);
+    case 3: return nt ? launch_t<float, float, true>(c, basis, 1, rb, s) : launch_t<float, float, false>(c, basis, 1, rb, s);
+    case 4: return nt ? launch_t<bf16, double, true>(c, basis, 0, rb, s) : launch_t<bf16, double, false>(c, basis, 0, rb, s);
+    case 5: return nt ? launch_t<bf16, float, true>(c, basis, 1, rb, s) : launch_t<bf16, float, false>(c, basis, 1, rb, s);
   }
   return hipErrorInvalidValue;
 }

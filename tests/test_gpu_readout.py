@@ -60,3 +60,16 @@ def check(m, got, steps):
 def test_few_states_at_tile_edges(basis, n, steps):
     m = model(n, min(n, 20), basis, 30)
     check(m, m.predict(steps), steps)
+
+
+@pytest.mark.parametrize("basis", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("n", [37, 1024, 1031])
+@pytest.mark.parametrize("steps", [16, 17, 32, 33, 64, 65, 96, 97, 128, 129, 200])
+def test_state_blocks_and_stores(basis, n, steps):
+    """Every number of state blocks per workgroup and a second block of them;
+    n = 1024: states on whole lines (streaming stores), else ordinary ones;
+    an output that starts one element off a line."""
+    m = model(n, 20, basis, 30)
+    check(m, m.predict(steps), steps)
+    space = torch.empty(steps * n + 1, dtype=m.dtype, device="cuda")
+    check(m, m.predict(steps, out=space[1:].view(steps, n)), steps)
