@@ -123,19 +123,20 @@ __device__ __forceinline__ int jacobi_sweeps(double* A, double* V, double* d, in
 // (the pair (d_j, e_j) is already singular), as are poles closer than that
 // (a Givens rotation moves their z weight onto one of them); the zero pole
 // is never deflated: a zero rho is raised to that tolerance.  Each root is
-// found by one 16-lane quarter-wavefront: bracketed iteration on the
+// found by a group of eight lanes: bracketed iteration on the
 // two-pole rational model of f (Li's "middle way"), from the root of a
 // two-pole model with the other terms frozen, falling back to bisection.
 constexpr int SEC_MAXIT = 64;
 constexpr double SEC_EPS = 2.220446049250313e-16;
-constexpr int SEC_TERMS = (MMAX + 15) / 16;   // secular terms per lane of a quarter-wave
+constexpr int SEC_TERMS = (MMAX + 7) / 8;   // secular terms per lane of an eight-lane group
+static_assert(MMAX <= CORE_THREADS / 8, "one group of eight lanes per root");
 
 struct SecShared {
   double dj[MMAX], zz[MMAX], zs[MMAX];   // live poles (descending), z^2, sign of z
   double rK[MMAX], mu[MMAX];             // root i: lambda_i = rK[i]^2 + mu[i]
   double zh[MMAX], nrm[2 * MMAX];
   double gc[MMAX], gs[MMAX], d[MMAX], z[MMAX];
-  int J[MMAX], gi[MMAX], gj[MMAX], dflist[MMAX], live[MMAX];
+  int J[MMAX], gi[MMAX], gj[MMAX], dflist[MMAX];
   int nd, ndef, ngiv, fail;
   double tol;
 };
@@ -150,10 +151,208 @@ __device__ __forceinline__ double recip(double x) {
   return r;
 }
 
-// lambda_i - d_j^2 = (d_K^2 - d_j^2) + mu_i, with d_K the pole root i is stored against
-__device__ __forceinline__ double lam_minus_d(const SecShared& S, int i, double dj) {
-  const double dK = S.rK[i];
-  return (dK - dj) * (dK + dj) + S.mu[i];
+// One Newton step (1e-15), and sqrt likewise from the reciprocal square root:
+// for the steps of the root iteration, which its tests check anyway.
+// recip1(0) is NaN.
+__device__ __forceinline__ double recip1(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+}
+__device__ __forceinline__ double sqrt1(double x) {
+  const double y = __builtin_amdgcn_rsq(x), g = x * y;
+  const double s = __builtin_fma(g, __builtin_fma(-0.5 * y, g, 0.5), g);
+  return x > 0.0 ? s : 0.0;
+}
+
+// Roots, z~ and singular vectors of the nd live poles.  NT: the term slots
+// per lane, at least ceil(nd / 8).  False when a root was not found.
+template <int NT>
+__device__ __forceinline__ bool secular_vectors(double* A, double* V, int r, int nd, SecShared& S, double* sdo) {
+  const int tid = threadIdx.x;
+  // Groups of eight lanes: root, z~ entry and column `grp` of the next three
+  // steps are one group's (MMAX <= 128 groups: one pass also at the largest
+  // rank, which took sixteen lanes a root two), its terms k = gl + 8 m in
+  // registers; dead slots hold a live pole with zero weight, so that no
+  // step tests for them.  These steps are bound by the FP64 issue rate (the
+  // scalar part of each root's iteration is repeated by its lanes), so
+  // fewer lanes per root and straight-line code count.
+  const int grp = tid >> 3, gl = tid & 7;
+  double tdj[NT], tzz[NT];
+#pragma unroll
+  for (int m = 0; m < NT; ++m) {
+    const int k = gl + 8 * m, kc = min(k, nd - 1);
+    tdj[m] = S.dj[kc];
+    tzz[m] = S.zz[kc];
+    tzz[m] = k < nd ? tzz[m] : 0.0;
+  }
+  double dK = 0.0, mu = 0.0;           // root grp: lambda = dK^2 + mu
+  if (grp < nd) {
+    const int i = grp;
+    int it = 0;
+    if (nd == 1) {
+      dK = S.dj[0];
+      mu = S.zz[0];
+    } else {
+      // the poles around the root (the two largest ones for the root above all)
+      const int ilo = i == 0 ? 1 : i, ihi = i == 0 ? 0 : i - 1;
+      const double plo = S.dj[ilo], phigh = S.dj[ihi], zlo = S.zz[ilo], zhi = S.zz[ihi];
+      const double half = 0.5 * (phigh - plo) * (phigh + plo);   // half the gap
+      double fm = 0.0, zsum = 0.0;     // f at the middle of the gap; sum of z^2
+#pragma unroll
+      for (int m = 0; m < NT; ++m) {
+        fm = __builtin_fma(tzz[m], recip1((tdj[m] - plo) * (tdj[m] + plo) - half), fm);
+        zsum += tzz[m];
+      }
+      fm = 1.0 + oct_sum(fm);
+      zsum = oct_sum(zsum);
+      const bool low = i > 0 && fm > 0.0;   // nearer to the lower pole
+      dK = low ? plo : phigh;
+      const double dlo = (plo - dK) * (plo + dK), dhi = (phigh - dK) * (phigh + dK);
+      double lo = i == 0 ? 0.0 : (low ? dlo : 0.5 * dlo);
+      double hi = i == 0 ? zsum : (low ? 0.5 * dhi : dhi);
+      double dsh[NT];           // d_k^2 - d_K^2
+#pragma unroll
+      for (int m = 0; m < NT; ++m) dsh[m] = (tdj[m] - dK) * (tdj[m] + dK);
+      mu = 0.5 * (lo + hi);
+      {
+        // Start from the root of the two-pole model: the two nearest terms
+        // exact, the others frozen at their midpoint value c,
+        //   c - z_K^2 / mu + z_O^2 / (del - mu) = 0
+        //   <=>  c mu^2 - (c del + z_K^2 + z_O^2) mu + z_K^2 del = 0,
+        // taken when it falls inside the bracket (else the midpoint).  A root
+        // far from the bracket's middle (a wide gap between the kept and the
+        // dropped directions) then needs a few iterations instead of ~9.
+        const double zK = low ? zlo : zhi, del = low ? dhi : dlo;
+        const double qa = __builtin_fma(zlo - zhi, recip1(half), fm);
+        const double qb = -(qa * del + zlo + zhi), qc = zK * del;
+        const double disc = qb * qb - 4.0 * qa * qc;
+        const double qq = -0.5 * (qb + __builtin_copysign(sqrt1(disc), qb));
+        const double g1 = qq * recip1(qa), g2 = qc * recip1(qq);
+        const bool guess = i > 0 && disc >= 0.0;
+        const bool in1 = g1 > lo && g1 < hi, in2 = g2 > lo && g2 < hi;
+        mu = guess && (in1 || in2) ? (in1 ? g1 : g2) : mu;
+      }
+      // the terms of the poles below (psi) and above (phi) the root
+      double tlo[NT], thi[NT];
+#pragma unroll
+      for (int m = 0; m < NT; ++m) {
+        const bool below = gl + 8 * m >= ilo;
+        tlo[m] = below ? tzz[m] : 0.0;
+        thi[m] = below ? 0.0 : tzz[m];
+      }
+      const double elo = i == 0 ? dhi : dlo, ehi = i == 0 ? INFINITY : dhi;   // the step's range
+      for (; it < SEC_MAXIT; ++it) {
+        double psi = 0.0, phi = 0.0, dpsi = 0.0, dphi = 0.0;
+#pragma unroll
+        for (int m = 0; m < NT; ++m) {
+          const double rinv = recip(dsh[m] - mu), rsq = rinv * rinv;
+          psi = __builtin_fma(tlo[m], rinv, psi);
+          phi = __builtin_fma(thi[m], rinv, phi);
+          dpsi = __builtin_fma(tlo[m], rsq, dpsi);
+          dphi = __builtin_fma(thi[m], rsq, dphi);
+        }
+        psi = oct_sum(psi);
+        phi = oct_sum(phi);
+        dpsi = oct_sum(dpsi);
+        dphi = oct_sum(dphi);
+        const double w = 1.0 + psi + phi;
+        hi = w > 0.0 ? mu : hi;
+        lo = w > 0.0 ? lo : mu;
+        if ((fabs(w) <= 8.0 * SEC_EPS * (1.0 + fabs(psi) + fabs(phi))) |
+            (hi - lo <= 4.0 * SEC_EPS * fmax(fabs(lo), fabs(hi))))
+          break;
+        // (the step only steers the iteration; the tests above decide
+        // convergence.  cq = 0 leaves r2, which is then the linear root)
+        const double Dlo = dlo - mu, Dhi = dhi - mu, dw = dpsi + dphi, DD = Dlo * Dhi;
+        const double cq = w - Dlo * dpsi - Dhi * dphi;
+        const double aq = (Dlo + Dhi) * w - DD * dw;
+        const double bq = DD * w;
+        const double disc = sqrt1(fabs(aq * aq - 4.0 * bq * cq));
+        const double qv = 0.5 * (aq + __builtin_copysign(disc, aq));
+        const double r1 = qv * recip1(cq), r2 = bq * recip1(qv), rn = -w * recip1(dw);
+        const double l1 = elo - mu, l2 = ehi - mu;
+        const bool v1 = (r1 > l1) & (r1 < l2), v2 = (r2 > l1) & (r2 < l2);
+        double eta = v1 ? r1 : r2;
+        eta = ((v1 | v2) & (w * eta < 0.0)) ? eta : rn;
+        const double nw = mu + eta;
+        mu = ((nw > lo) & (nw < hi)) ? nw : 0.5 * (lo + hi);
+      }
+    }
+    if (gl == 0) {
+      S.rK[i] = dK;
+      S.mu[i] = mu;
+      if (it >= SEC_MAXIT || !isfinite(mu)) S.fail = 1;
+    }
+  }
+  __syncthreads();
+  if (S.fail) return false;
+
+  // z~ from the computed roots (Loewner's formula), the product split over
+  // the group's lanes
+  if (grp < nd) {
+    const double dj = S.dj[grp];
+    double prod = 1.0;
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      const int i = gl + 8 * m, ic = min(i, nd - 1);
+      const double rK = S.rK[ic], lam = (rK - dj) * (rK + dj) + S.mu[ic];   // lambda_i - d_j^2
+      const double den = recip((tdj[m] - dj) * (tdj[m] + dj));
+      const double f = i == grp ? lam : lam * den;
+      prod *= i < nd ? f : 1.0;
+    }
+    prod = oct_prod(prod);
+    if (gl == 0) S.zh[grp] = S.zs[grp] * sqrt(fmax(prod, 0.0));
+  }
+  __syncthreads();
+  // Vectors of the roots: the unnormalised entries on the live rows J[jj]
+  // (zero on the deflated rows), their norms, then U columns of length
+  // sigma'_i and V columns of length 1, and the finite check, with no
+  // barrier in between.
+  if (grp < nd) {
+    const int i = grp;
+    double ea[NT], ev[NT];
+    int row[NT];
+    double sa = 0.0, sv = 0.0;
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      const int jc = min(gl + 8 * m, nd - 1);
+      row[m] = S.J[jc];
+      ea[m] = S.zh[jc];
+    }
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      const double dj = tdj[m];
+      const bool in = gl + 8 * m < nd;
+      const double a = ea[m] * recip(-((dK - dj) * (dK + dj) + mu));   // z~_j / (d_j^2 - lambda_i)
+      ea[m] = in ? a : 0.0;
+      ev[m] = in ? (row[m] == r ? -1.0 : dj * a) : 0.0;
+      sa = __builtin_fma(ea[m], ea[m], sa);
+      sv = __builtin_fma(ev[m], ev[m], sv);
+    }
+    sa = oct_sum(sa);
+    sv = oct_sum(sv);
+    const double fa = sqrt(dK * dK + mu) / sqrt(sa);   // sigma' / |u|
+    const double fv = 1.0 / sqrt(sv);
+    double sn = 0.0;
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      const double a = ea[m] * fa;
+      sn = __builtin_fma(a, a, sn);
+      if (gl + 8 * m < nd) {
+        A[i * LDK + row[m]] = a;
+        V[i * LDK + row[m]] = ev[m] * fv;
+      }
+    }
+    sn = oct_sum(sn);
+    if (gl == 0) sdo[i] = sqrt(sn);          // the column norm of what A holds
+    for (int t = gl; t < S.ndef; t += 8) {
+      A[i * LDK + S.dflist[t]] = 0.0;
+      V[i * LDK + S.dflist[t]] = 0.0;
+    }
+    // an entry that is not finite makes its column's sum not finite
+    if (!(isfinite(sn) && isfinite(sv) && isfinite(fv))) S.fail = 1;
+  }
+  return true;
 }
 
 // Returns true on success; fills A (columns U_k * sigma'), V (V_k), column
@@ -176,8 +375,7 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
     double m = 0.0;
     for (int j = tid; j < r; j += 64) m = fmax(m, fmax(fabs(sig[j]), fabs(pv[j])));
     if (tid == 0) m = fmax(m, fabs(rho));
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    m = wave_max(m);
     const double tl = 8.0 * SEC_EPS * m;
     const double rz = fabs(rho) <= tl ? tl : rho;
     const double d0 = j0 < r ? sig[j0] : 0.0, z0 = j0 < r ? pv[j0] : rz;
@@ -196,12 +394,19 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
     const unsigned long long lt = (tid == 0) ? 0ull : (~0ull >> (64 - tid));
     const int p0 = __popcll(m0 & lt), p1 = __popcll(m1 & lt);
     const int nl0 = __popcll(m0), nd0 = min(n, 64) - nl0;
+    // live pole k is entry j
+    auto stage = [&](int k, int j, double dj, double zj) {
+      S.J[k] = j;
+      S.dj[k] = dj;
+      S.zz[k] = zj * zj;
+      S.zs[k] = zj < 0.0 ? -1.0 : 1.0;
+    };
     if (j0 < n) {
-      if (l0) S.live[p0] = j0;
+      if (l0) stage(p0, j0, d0, z0);
       else S.dflist[j0 - p0] = j0;
     }
     if (j1 < n) {
-      if (l1) S.live[nl0 + p1] = j1;
+      if (l1) stage(nl0 + p1, j1, d1, z1);
       else S.dflist[nd0 + (j1 - 64 - p1)] = j1;
     }
     int nl = nl0 + __popcll(m1), ndef = n - nl;
@@ -211,15 +416,14 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
     // tied poles (rare): detected in parallel, merged serially by lane 0
     bool tie = false;
     for (int k = tid; k + 1 < nl; k += 64) {
-      const int i = S.live[k], j = S.live[k + 1];
-      tie = tie || (j != r && S.d[i] - S.d[j] <= tl);
+      tie = tie || (S.J[k + 1] != r && S.dj[k] - S.dj[k + 1] <= tl);
     }
     int ngiv = 0;
     if (__ballot(tie)) {
       if (tid == 0) {
         int k = 0;
         while (k + 1 < nl) {
-          const int i = S.live[k], j = S.live[k + 1];
+          const int i = S.J[k], j = S.J[k + 1];
           if (j != r && S.d[i] - S.d[j] <= tl) {
             const double h = hypot(S.z[i], S.z[j]);
             S.gc[ngiv] = S.z[i] / h;
@@ -229,7 +433,7 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
             ++ngiv;
             S.z[i] = h;
             S.dflist[ndef++] = j;
-            for (int t = k + 1; t + 1 < nl; ++t) S.live[t] = S.live[t + 1];
+            for (int t = k + 1; t + 1 < nl; ++t) S.J[t] = S.J[t + 1];
             --nl;
           } else {
             ++k;
@@ -242,14 +446,7 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    for (int t = tid; t < nl; t += 64) {
-      const int j = S.live[t];
-      const double zj = S.z[j];
-      S.J[t] = j;
-      S.dj[t] = S.d[j];
-      S.zz[t] = zj * zj;
-      S.zs[t] = zj < 0.0 ? -1.0 : 1.0;
+      for (int t = tid; t < nl; t += 64) stage(t, S.J[t], S.d[S.J[t]], S.z[S.J[t]]);
     }
     if (tid == 0) {
       S.tol = tl;
@@ -262,198 +459,13 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
   __syncthreads();
   const int nd = S.nd;
 
-  // roots: one 16-lane quarter-wave each, the lane's terms kept in registers
-  const int qw = tid >> 4, ql = tid & 15;
-  double tdj[SEC_TERMS], tzz[SEC_TERMS];
-#pragma unroll
-  for (int m = 0; m < SEC_TERMS; ++m) {
-    const int k = ql + 16 * m;
-    tdj[m] = k < nd ? S.dj[k] : 0.0;
-    tzz[m] = k < nd ? S.zz[k] : 0.0;
-  }
-  for (int i = qw; i < nd; i += CORE_THREADS / 16) {
-    if (nd == 1) {
-      if (ql == 0) {
-        S.rK[0] = S.dj[0];
-        S.mu[0] = S.zz[0];
-      }
-      continue;
-    }
-    int K = 0;
-    double fm = 0.0, half = 0.0;   // f at the midpoint of (d_i^2, d_{i-1}^2), half the gap
-    if (i > 0) {
-      const double dI = S.dj[i];
-      half = 0.5 * (S.dj[i - 1] - dI) * (S.dj[i - 1] + dI);
-#pragma unroll
-      for (int m = 0; m < SEC_TERMS; ++m)
-        if (ql + 16 * m < nd) fm += tzz[m] * recip((tdj[m] - dI) * (tdj[m] + dI) - half);
-      fm = 1.0 + row_sum(fm);
-      K = fm > 0.0 ? i : i - 1;
-    }
-    const double dK = S.dj[K];
-    double lo, hi;
-    if (i == 0) {
-      double zsum = 0.0;
-#pragma unroll
-      for (int m = 0; m < SEC_TERMS; ++m) zsum += tzz[m];
-      lo = 0.0;
-      hi = row_sum(zsum);
-    } else {
-      lo = (S.dj[i] - dK) * (S.dj[i] + dK);
-      hi = (S.dj[i - 1] - dK) * (S.dj[i - 1] + dK);
-      if (K == i) hi *= 0.5;
-      else lo *= 0.5;
-    }
-    const int ilo = i == 0 ? 1 : i, ihi = i == 0 ? 0 : i - 1;
-    const double dlo = (S.dj[ilo] - dK) * (S.dj[ilo] + dK);
-    const double dhi = (S.dj[ihi] - dK) * (S.dj[ihi] + dK);
-    double dsh[SEC_TERMS];   // d_k^2 - d_K^2
-#pragma unroll
-    for (int m = 0; m < SEC_TERMS; ++m) dsh[m] = (tdj[m] - dK) * (tdj[m] + dK);
-    double mu = 0.5 * (lo + hi);
-    if (i > 0) {
-      // Start from the root of the two-pole model: the two nearest terms
-      // exact, the others frozen at their midpoint value c,
-      //   c - z_K^2 / mu + z_O^2 / (del - mu) = 0
-      //   <=>  c mu^2 - (c del + z_K^2 + z_O^2) mu + z_K^2 del = 0,
-      // taken when it falls inside the bracket (else the midpoint).  A root
-      // far from the bracket's middle (a wide gap between the kept and the
-      // dropped directions) then needs a few iterations instead of ~9.
-      const double zK = S.zz[K], zO = S.zz[K == i ? i - 1 : i];
-      const double del = K == i ? dhi : dlo;
-      const double c0 = fm + (S.zz[i] - S.zz[i - 1]) / half;
-      const double qa = c0, qb = -(c0 * del + zK + zO), qc = zK * del;
-      const double disc = qb * qb - 4.0 * qa * qc;
-      if (disc >= 0.0) {
-        const double qq = -0.5 * (qb + (qb >= 0.0 ? sqrt(disc) : -sqrt(disc)));
-        const double g1 = qa != 0.0 ? qq / qa : NAN;
-        const double g2 = qq != 0.0 ? qc / qq : NAN;
-        if (g1 > lo && g1 < hi) mu = g1;
-        else if (g2 > lo && g2 < hi) mu = g2;
-      }
-    }
-    int it = 0;
-    const int nterm = (nd + 15) >> 4;   // term slots holding a live pole
-    for (; it < SEC_MAXIT; ++it) {
-      double psi = 0.0, phi = 0.0, dpsi = 0.0, dphi = 0.0;
-#pragma unroll
-      for (int m = 0; m < SEC_TERMS; ++m) {
-        if (m >= nterm) break;            // uniform
-        const int k = ql + 16 * m;
-        if (k < nd) {
-          const double rinv = recip(dsh[m] - mu);
-          const double t = tzz[m] * rinv;
-          if (k >= ilo) {
-            psi += t;
-            dpsi += t * rinv;
-          } else {
-            phi += t;
-            dphi += t * rinv;
-          }
-        }
-      }
-      psi = row_sum(psi);
-      phi = row_sum(phi);
-      dpsi = row_sum(dpsi);
-      dphi = row_sum(dphi);
-      const double w = 1.0 + psi + phi;
-      if (w > 0.0) hi = mu;
-      else lo = mu;
-      if (fabs(w) <= 8.0 * SEC_EPS * (1.0 + fabs(psi) + fabs(phi)) ||
-          hi - lo <= 4.0 * SEC_EPS * fmax(fabs(lo), fabs(hi)))
-        break;
-      const double Dlo = dlo - mu, Dhi = dhi - mu, dw = dpsi + dphi;
-      const double cq = w - Dlo * dpsi - Dhi * dphi;
-      const double aq = (Dlo + Dhi) * w - Dlo * Dhi * dw;
-      const double bq = Dlo * Dhi * w;
-      // (the step only steers the iteration; the tests above decide
-      // convergence, so reciprocals stand in for the divisions)
-      double r1 = NAN, r2 = NAN;
-      if (cq == 0.0) {
-        if (aq != 0.0) r1 = bq * recip(aq);
-      } else {
-        const double disc = sqrt(fabs(aq * aq - 4.0 * bq * cq));
-        const double qv = 0.5 * (aq + (aq >= 0.0 ? disc : -disc));
-        r1 = qv * recip(cq);
-        if (qv != 0.0) r2 = bq * recip(qv);
-      }
-      double eta;
-      if (i == 0) eta = (r1 > Dhi) ? r1 : ((r2 > Dhi) ? r2 : NAN);
-      else eta = (r1 > Dlo && r1 < Dhi) ? r1 : ((r2 > Dlo && r2 < Dhi) ? r2 : NAN);
-      if (!(eta == eta) || w * eta >= 0.0) eta = -w * recip(dw);
-      double nw = mu + eta;
-      if (!(nw > lo && nw < hi)) nw = 0.5 * (lo + hi);
-      mu = nw;
-    }
-    if (ql == 0) {
-      S.rK[i] = dK;
-      S.mu[i] = mu;
-      if (it >= SEC_MAXIT || !isfinite(mu)) S.fail = 1;
-    }
-  }
-  __syncthreads();
-  if (S.fail) return false;
-
-  // z~ from the computed roots (Loewner's formula), one quarter-wave per
-  // entry, the product split over its 16 lanes
-  for (int jj = qw; jj < nd; jj += CORE_THREADS / 16) {
-    const double dj = S.dj[jj];
-    double prod = 1.0;
-    for (int i = ql; i < nd; i += 16) {
-      const double di = S.dj[i];
-      prod *= i == jj ? lam_minus_d(S, jj, dj) : lam_minus_d(S, i, dj) * recip((di - dj) * (di + dj));
-    }
-    prod = row_prod(prod);
-    if (ql == 0) S.zh[jj] = S.zs[jj] * sqrt(fmax(prod, 0.0));
-  }
-  __syncthreads();
-  // Vectors of the roots, one quarter-wave per column i: the unnormalised
-  // entries on the live rows J[jj] (zero on the deflated rows), their norms,
-  // then U columns of length sigma'_i and V columns of length 1, and the
-  // finite check, with no barrier in between.
-  for (int i = qw; i < nd; i += CORE_THREADS / 16) {
-    double ea[SEC_TERMS], ev[SEC_TERMS];
-    double sa = 0.0, sv = 0.0;
-#pragma unroll
-    for (int m = 0; m < SEC_TERMS; ++m) {
-      const int jj = ql + 16 * m;
-      ea[m] = 0.0;
-      ev[m] = 0.0;
-      if (jj < nd) {
-        const double dj = S.dj[jj];
-        const double a = S.zh[jj] * recip(-lam_minus_d(S, i, dj));   // z~_j / (d_j^2 - lambda_i)
-        ea[m] = a;
-        ev[m] = S.J[jj] == r ? -1.0 : dj * a;
-        sa = __builtin_fma(a, a, sa);
-        sv = __builtin_fma(ev[m], ev[m], sv);
-      }
-    }
-    sa = row_sum(sa);
-    sv = row_sum(sv);
-    const double fa = sqrt(S.rK[i] * S.rK[i] + S.mu[i]) / sqrt(sa);
-    const double fv = 1.0 / sqrt(sv);
-    bool bad = false;
-    double sn = 0.0;
-#pragma unroll
-    for (int m = 0; m < SEC_TERMS; ++m) {
-      const int jj = ql + 16 * m;
-      if (jj < nd) {
-        const int row = S.J[jj];
-        const double a = ea[m] * fa, v = ev[m] * fv;
-        A[i * LDK + row] = a;
-        V[i * LDK + row] = v;
-        sn = __builtin_fma(a, a, sn);
-        bad = bad || !isfinite(a) || !isfinite(v);
-      }
-    }
-    sn = row_sum(sn);
-    if (ql == 0) sdo[i] = sqrt(sn);          // the column norm of what A holds
-    for (int t = ql; t < S.ndef; t += 16) {
-      A[i * LDK + S.dflist[t]] = 0.0;
-      V[i * LDK + S.dflist[t]] = 0.0;
-    }
-    if (bad) S.fail = 1;
-  }
+  // (straight-line code for the term slots in use: a run-time count made the
+  // compiler index registers)
+  bool ok;
+  if (nd <= 24) ok = secular_vectors<3>(A, V, r, nd, S, sdo);
+  else if (nd <= 48) ok = secular_vectors<6>(A, V, r, nd, S, sdo);
+  else ok = secular_vectors<SEC_TERMS>(A, V, r, nd, S, sdo);
+  if (!ok) return false;
   // deflated pairs: (d_j, e_j, e_j)
   for (int t = tid; t < S.ndef; t += CORE_THREADS) sdo[nd + t] = fabs(sig[S.dflist[t]]);
   for (int idx = tid; idx < S.ndef * n; idx += CORE_THREADS) {
@@ -499,36 +511,53 @@ typedef double d4_t __attribute__((ext_vector_type(4)));
 // One 16 x 16 FP64 tile D = sum_{k < K} A(row, k) B(k, col) on the matrix
 // cores, in the 16x16x4 operand layout: lane l holds row (and column) l % 16
 // and k-step offset l / 16, and reads its elements at pa[k * sa] and
-// pb[k * sb].  Every load is issued (a lane whose row or column is out of
-// range, use_a / use_b false, or whose k is past K, reads k = 0 of a valid
-// pointer and passes zero), so the loop has no divergent branches; two
-// accumulators over alternate k-steps keep two products in flight, and the
-// next eight k-steps' operands are loaded while these are multiplied.
+// pb[k * sb].  A lane whose row or column is out of range passes any valid
+// pointer: what it reads reaches only elements of D out of range, which the
+// callers drop.  Two accumulators over alternate k-steps keep two products
+// in flight, and the next eight k-steps' operands are loaded while these
+// are multiplied.
+struct TileOps {
+  const double *a, *b;
+  int sa, sb;
+  __device__ __forceinline__ TileOps(const double* pa, int sa_, const double* pb, int sb_, int l)
+      : a(pa + (l >> 4) * sa_), b(pb + (l >> 4) * sb_), sa(4 * sa_), sb(4 * sb_) {}
+  // the next eight k-steps, all below K
+  __device__ __forceinline__ void load(double& a0, double& b0, double& a1, double& b1) {
+    a0 = a[0];
+    b0 = b[0];
+    a1 = a[sa];
+    b1 = b[sb];
+    a += 2 * sa;
+    b += 2 * sb;
+  }
+  // the last ones, kl = K minus the lane's k: zero past K (read at k - 4 or at the start there)
+  __device__ __forceinline__ void load_last(int left, const double* pa, const double* pb, double& a0, double& b0,
+                                            double& a1, double& b1) {
+    const bool v0 = left > 0, v1 = left > 4;
+    a0 = v0 ? a[0] : pa[0];
+    b0 = v0 ? b[0] : pb[0];
+    a1 = v1 ? a[sa] : pa[0];
+    b1 = v1 ? b[sb] : pb[0];
+    a0 = v0 ? a0 : 0.0;
+    b0 = v0 ? b0 : 0.0;
+    a1 = v1 ? a1 : 0.0;
+    b1 = v1 ? b1 : 0.0;
+  }
+};
+
 template <int NB>
-__device__ __forceinline__ d4_t mfma_tile_nb(const double* pa, int sa, bool use_a, const double* pb, int sb,
-                                             bool use_b, int K, int l) {
+__device__ __forceinline__ d4_t mfma_tile_nb(const double* pa, int sa, const double* pb, int sb, int K, int l) {
   d4_t d0 = {0.0, 0.0, 0.0, 0.0}, d1 = d0;
-  const int kl = l >> 4;
-  // operands of the k-steps k0 + kl and k0 + kl + 4 (zero past K)
-  auto load = [&](int k0, double& a0, double& b0, double& a1, double& b1) {
-    const int ka = k0 + kl, kb = ka + 4;
-    const bool va = ka < K, vb = kb < K;
-    const int ia = va ? ka : 0, ib = vb ? kb : 0;
-    a0 = pa[ia * sa];
-    b0 = pb[ia * sb];
-    a1 = pa[ib * sa];
-    b1 = pb[ib * sb];
-    a0 = use_a && va ? a0 : 0.0;
-    b0 = use_b && va ? b0 : 0.0;
-    a1 = use_a && vb ? a1 : 0.0;
-    b1 = use_b && vb ? b1 : 0.0;
-  };
+  TileOps t(pa, sa, pb, sb, l);
+  const int left = K - 8 * (NB - 1) - (l >> 4);
   double a0, b0, a1, b1;
-  load(0, a0, b0, a1, b1);
+  if (NB > 1) t.load(a0, b0, a1, b1);
+  else t.load_last(left, pa, pb, a0, b0, a1, b1);
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    double na0, nb0, na1, nb1;
-    load(8 * j + 8, na0, nb0, na1, nb1);   // the next k-steps' loads overlap these products
+    double na0 = 0.0, nb0 = 0.0, na1 = 0.0, nb1 = 0.0;
+    if (j < NB - 2) t.load(na0, nb0, na1, nb1);   // the next k-steps' loads overlap these products
+    else if (j == NB - 2) t.load_last(left, pa, pb, na0, nb0, na1, nb1);
     d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, d0, 0, 0, 0);
     d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, d1, 0, 0, 0);
     a0 = na0;
@@ -539,36 +568,18 @@ __device__ __forceinline__ d4_t mfma_tile_nb(const double* pa, int sa, bool use_
   return d0 + d1;
 }
 
-// The same product with a run-time loop over the blocks (fewer registers;
-// the BF16 Gram correction's rarely taken products)
-__device__ __forceinline__ d4_t mfma_tile_loop(const double* pa, int sa, bool use_a, const double* pb, int sb,
-                                               bool use_b, int K, int l) {
+// The same product with a run-time loop over the blocks (less code; the
+// BF16 Gram correction's rarely taken products)
+__device__ __forceinline__ d4_t mfma_tile_loop(const double* pa, int sa, const double* pb, int sb, int K, int l) {
   d4_t d0 = {0.0, 0.0, 0.0, 0.0}, d1 = d0;
-  const int kl = l >> 4;
-  auto load = [&](int k0, double& a0, double& b0, double& a1, double& b1) {
-    const int ka = k0 + kl, kb = ka + 4;
-    const bool va = ka < K, vb = kb < K;
-    const int ia = va ? ka : 0, ib = vb ? kb : 0;
-    a0 = pa[ia * sa];
-    b0 = pb[ia * sb];
-    a1 = pa[ib * sa];
-    b1 = pb[ib * sb];
-    a0 = use_a && va ? a0 : 0.0;
-    b0 = use_b && va ? b0 : 0.0;
-    a1 = use_a && vb ? a1 : 0.0;
-    b1 = use_b && vb ? b1 : 0.0;
-  };
-  double a0, b0, a1, b1;
-  load(0, a0, b0, a1, b1);
-  for (int k0 = 0; k0 < K; k0 += 8) {
-    double na0, nb0, na1, nb1;
-    load(k0 + 8, na0, nb0, na1, nb1);
+  TileOps t(pa, sa, pb, sb, l);
+  const int nb = (K + 7) >> 3, left = K - 8 * (nb - 1) - (l >> 4);
+  for (int j = 0; j < nb; ++j) {
+    double a0, b0, a1, b1;
+    if (j < nb - 1) t.load(a0, b0, a1, b1);
+    else t.load_last(left, pa, pb, a0, b0, a1, b1);
     d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, d0, 0, 0, 0);
     d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, d1, 0, 0, 0);
-    a0 = na0;
-    b0 = nb0;
-    a1 = na1;
-    b1 = nb1;
   }
   return d0 + d1;
 }
@@ -579,19 +590,18 @@ __device__ __forceinline__ d4_t mfma_tile_loop(const double* pa, int sa, bool us
 // K = 40 on one wavefront), its load waits and branches breaking the
 // pipelining.  The products and their order are those of the loop, bit for
 // bit.
-__device__ __forceinline__ d4_t mfma_tile(const double* pa, int sa, bool use_a, const double* pb,
-                                          int sb, bool use_b, int K, int l) {
+__device__ __forceinline__ d4_t mfma_tile(const double* pa, int sa, const double* pb, int sb, int K, int l) {
   static_assert(MMAX <= 72, "K of the core's products is at most 72");
   switch ((K + 7) >> 3) {
-    case 1: return mfma_tile_nb<1>(pa, sa, use_a, pb, sb, use_b, K, l);
-    case 2: return mfma_tile_nb<2>(pa, sa, use_a, pb, sb, use_b, K, l);
-    case 3: return mfma_tile_nb<3>(pa, sa, use_a, pb, sb, use_b, K, l);
-    case 4: return mfma_tile_nb<4>(pa, sa, use_a, pb, sb, use_b, K, l);
-    case 5: return mfma_tile_nb<5>(pa, sa, use_a, pb, sb, use_b, K, l);
-    case 6: return mfma_tile_nb<6>(pa, sa, use_a, pb, sb, use_b, K, l);
-    case 7: return mfma_tile_nb<7>(pa, sa, use_a, pb, sb, use_b, K, l);
-    case 8: return mfma_tile_nb<8>(pa, sa, use_a, pb, sb, use_b, K, l);
-    case 9: return mfma_tile_nb<9>(pa, sa, use_a, pb, sb, use_b, K, l);
+    case 1: return mfma_tile_nb<1>(pa, sa, pb, sb, K, l);
+    case 2: return mfma_tile_nb<2>(pa, sa, pb, sb, K, l);
+    case 3: return mfma_tile_nb<3>(pa, sa, pb, sb, K, l);
+    case 4: return mfma_tile_nb<4>(pa, sa, pb, sb, K, l);
+    case 5: return mfma_tile_nb<5>(pa, sa, pb, sb, K, l);
+    case 6: return mfma_tile_nb<6>(pa, sa, pb, sb, K, l);
+    case 7: return mfma_tile_nb<7>(pa, sa, pb, sb, K, l);
+    case 8: return mfma_tile_nb<8>(pa, sa, pb, sb, K, l);
+    case 9: return mfma_tile_nb<9>(pa, sa, pb, sb, K, l);
     default: return d4_t{0.0, 0.0, 0.0, 0.0};   // K <= 0
   }
 }
@@ -605,66 +615,63 @@ __device__ __forceinline__ d4_t mfma_tile(const double* pa, int sa, bool use_a, 
 // LDK + i]; sQ is free here (Q' is written) and receives E V_k.
 __device__ __forceinline__ void general_tail(const CoreArgs& c, int r, int rn, int M, double qy,
                                           const double* sA, const double* sV, const double* sC,
-                                          double* sQ, const double* sd, const double* sgn,
-                                          const double* pyr, const double* qB, const int* perm) {
+                                          double* sQ, const double* sgn, const double* pyr, const double* qB, const int* perm) {
   DevState* __restrict__ st = c.st;
   DevState* __restrict__ tst = c.tst;
   const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
   const int trefold = tst->refold;            // the T sweep left T[:, :r] = B (R = I)
   const int mTe = trefold ? r : tst->m;       // stored T columns before y; y sits in column mTe
-  // E V_k[:, kept] (M x rn, K = M) into sQ[b * MMAX + i]
-  {
-    const int ntr = (M + 15) / 16, ntc = (rn + 15) / 16;
-    for (int tile = wv; tile < ntr * ntc; tile += CORE_THREADS / 64) {
+  // R (global), whose loads pass under the products of E V_k, then to sQ
+  constexpr int NQ = (CMAX * RMAX + CORE_THREADS - 1) / CORE_THREADS;
+  double rr[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) rr[i] = tst->Q[min(tid + i * CORE_THREADS, CMAX * RMAX - 1)];
+  // E V_k[:, kept] (M x rn, K = M), its tiles in registers until sQ is free
+  constexpr int NET = ((MMAX + 15) / 16) * ((RMAX + 15) / 16);
+  static_assert(NET <= 2 * (CORE_THREADS / 64), "two tiles of E V_k per wave at most");
+  const int ntr = (M + 15) / 16, ntc = (rn + 15) / 16;
+  d4_t et[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int tile = wv + 16 * h;
+    if (tile < ntr * ntc) {
       const int i0 = 16 * (tile % ntr), b0 = 16 * (tile / ntr);
       const int ia = i0 + (l & 15), bb = b0 + (l & 15);
       const int pb = bb < rn ? perm[bb] : 0;
       // columns j < r of E on the matrix cores (row ia: row ia of G, stride
       // RMAX along j, or q^T B), then column r (U^T y, q^T y) times row r of
       // V_k as an outer-product term
-      d4_t d = mfma_tile(ia < r ? sC + ia : qB, ia < r ? RMAX : 1, ia <= r, sV + pb * LDK, 1, bb < rn,
-                         r, l);
-      const double vr = bb < rn ? sV[pb * LDK + r] : 0.0;
+      d4_t d = mfma_tile(ia < r ? sC + ia : qB, ia < r ? RMAX : 1, sV + pb * LDK, 1, r, l);
+      const double vr = sV[pb * LDK + r];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int i = i0 + 4 * v + (l >> 4);
         const double er = i < r ? pyr[i < r ? i : 0] : (i == r ? qy : 0.0);
         d[v] = __builtin_fma(er, vr, d[v]);
-        if (i < M && bb < rn) sQ[bb * MMAX + i] = d[v];
       }
+      et[h] = d;
     }
   }
-  // R' tiles in registers (R is read from the T state, rewritten in place
-  // after the barrier below)
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    const int idx = tid + i * CORE_THREADS, c0 = idx / RMAX, j = idx % RMAX;
+    if (idx < CMAX * RMAX) sQ[c0 * LDQ + j] = c0 < mTe && j < r ? rr[i] : 0.0;
+  }
+  __syncthreads();
+  // R' = [[R, 0], [0, 1]] V_k, 16 x 16 tiles in registers; those past the
+  // live rows and columns are zero
   constexpr int NRT = 4 * ((CMAX + 15) / 16);
+  static_assert(NRT <= 2 * (CORE_THREADS / 64), "two R' tiles per wave at most");
   d4_t rt[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int tile = wv + 16 * h;
     d4_t d = {0.0, 0.0, 0.0, 0.0};
-    if (tile < NRT) {
-      const int c0 = 16 * (tile >> 2), k0 = 16 * (tile & 3);
-      const int kb = k0 + (l & 15);
+    const int c0 = 16 * (tile >> 2), k0 = 16 * (tile & 3);
+    if (tile < NRT && c0 <= mTe && k0 < rn) {
+      const int kb = k0 + (l & 15), ca = min(c0 + (l & 15), CMAX - 1);
       const int pk = kb < rn ? perm[kb] : 0;
-      if (!trefold) {
-        // R (global, L2) for all k-steps first: one round of latency
-        constexpr int KS = RMAX / 4;
-        const int ca = c0 + (l & 15);
-        double av[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const int j = 4 * ks + (l >> 4);
-          av[ks] = (j < r && ca < mTe) ? tst->Q[ca * RMAX + j] : 0.0;
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          if (4 * ks < r) {
-            const int j = 4 * ks + (l >> 4);
-            const double bv = (j < r && kb < rn) ? sV[pk * LDK + j] : 0.0;
-            d = __builtin_amdgcn_mfma_f64_16x16x4f64(av[ks], bv, d, 0, 0, 0);
-          }
-        }
-      }
+      if (!trefold) d = mfma_tile(sQ + ca * LDQ, 1, sV + pk * LDK, 1, r, l);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int cr = c0 + 4 * v + (l >> 4);
@@ -679,6 +686,19 @@ __device__ __forceinline__ void general_tail(const CoreArgs& c, int r, int rn, i
     rt[h] = d;
   }
   __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int tile = wv + 16 * h;
+    if (tile < ntr * ntc) {
+      const int i0 = 16 * (tile % ntr), b0 = 16 * (tile / ntr), bb = b0 + (l & 15);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = i0 + 4 * v + (l >> 4);
+        if (i < M && bb < rn) sQ[bb * MMAX + i] = et[h][v];
+      }
+    }
+  }
+  __syncthreads();
   // G' = U_k^T (E V_k) (rn x rn, K = M) and A~ = G' diag(sigma')^-1, each
   // tile formed transposed (as for C in the chained update: lane l holds
   // rows i0 + l%16, so the stores write 128-byte pieces)
@@ -688,13 +708,12 @@ __device__ __forceinline__ void general_tail(const CoreArgs& c, int r, int rn, i
       const int i0 = 16 * (tile % nt), j0 = 16 * (tile / nt);
       const int ia = i0 + (l & 15), jb = j0 + (l & 15);
       const int pa = ia < rn ? perm[ia] : 0;
-      const d4_t d = mfma_tile(sQ + (jb < rn ? jb : 0) * MMAX, 1, jb < rn, sA + pa * LDK, 1, ia < rn,
-                               M, l);
+      const d4_t d = mfma_tile(sQ + (jb < rn ? jb : 0) * MMAX, 1, sA + pa * LDK, 1, M, l);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int j = j0 + 4 * v + (l >> 4);
         if (ia < rn && j < rn) {
-          const double g = d[v] / sd[pa];
+          const double g = d[v] / sgn[ia];
           st->C[j * RMAX + ia] = g;
           st->At[j * RMAX + ia] = g / sgn[j];
         }
@@ -769,8 +788,7 @@ __device__ void gram_fix(const CoreArgs& c, int r, double* sA, double* sV, doubl
   for (int it = 0; it < 12; ++it) {
     int far = 0;
     if (tile_live) {
-      const d4_t d = mfma_tile_loop(sV + (ra < r ? ra : 0), LDK, ra < r, sA + (cb < r ? cb : 0) * LDK, 1,
-                               cb < r, r, l);
+      const d4_t d = mfma_tile_loop(sV + (ra < r ? ra : 0), LDK, sA + (cb < r ? cb : 0) * LDK, 1, r, l);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int i = row0 + 4 * v + (l >> 4), j = cb;
@@ -784,8 +802,8 @@ __device__ void gram_fix(const CoreArgs& c, int r, double* sA, double* sV, doubl
     const int more = __syncthreads_or(far);
     d4_t yt = {0.0, 0.0, 0.0, 0.0}, tz = yt;
     if (tile_live) {
-      yt = mfma_tile_loop(sA + (ra < r ? ra : 0), LDK, ra < r, sQ + (cb < r ? cb : 0) * LDQ, 1, cb < r, r, l);
-      tz = mfma_tile_loop(sQ + (ra < r ? ra : 0), LDQ, ra < r, sV + (cb < r ? cb : 0) * LDK, 1, cb < r, r, l);
+      yt = mfma_tile_loop(sA + (ra < r ? ra : 0), LDK, sQ + (cb < r ? cb : 0) * LDQ, 1, r, l);
+      tz = mfma_tile_loop(sQ + (ra < r ? ra : 0), LDQ, sV + (cb < r ? cb : 0) * LDK, 1, r, l);
     }
     __syncthreads();
     if (tile_live) {
@@ -833,8 +851,9 @@ __device__ void gram_fix(const CoreArgs& c, int r, double* sA, double* sV, doubl
 template <bool GENERAL>
 __device__ __forceinline__ void core_update(const CoreArgs& c) {
   DevState* __restrict__ st = c.st;
-  __shared__ double sA[MMAX * LDK];
-  __shared__ double sV[MMAX * LDK];
+  __shared__ double sAV[2 * MMAX * LDK];   // K V_k and V_k
+  double* const sA = sAV;
+  double* const sV = sAV + MMAX * LDK;
   __shared__ double red[CORE_THREADS];
   __shared__ double tot[PW];
   __shared__ double sd[MMAX + 1];
@@ -869,7 +888,9 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   constexpr int nslot = CORE_THREADS / (PW / 2);
   constexpr int RU = 10;
   const bool rth = tid < nslot * pw2;
-  const int rg = rth ? tid % pw2 : 0, rsl = rth ? tid / pw2 : 0;
+  // (tid / pw2 in float: exact, the quotients keep 0.5 / pw2 from a whole number)
+  const int rq = (int)(((float)tid + 0.5f) * __builtin_amdgcn_rcpf((float)pw2));
+  const int rg = rth ? tid - rq * pw2 : 0, rsl = rth ? rq : 0;
   const double2* __restrict__ rec = reinterpret_cast<const double2*>(c.partials);
   double2 rv[RU];
   int64_t macc0 = 0;
@@ -880,6 +901,7 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   auto load_records = [&](int ch) {
 #pragma unroll
     for (int i = 0; i < RU; ++i) {
+      if ((ch * RU + i) * nslot >= c.nblk) break;   // uniform
       const int b = rsl + (ch * RU + i) * nslot;
       rv[i] = rec[(int64_t)(b < c.nblk ? b : 0) * (PW / 2) + rg];
     }
@@ -899,14 +921,11 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int idx = tid + i * CORE_THREADS;
-      const int c0 = idx / RMAX, j = idx % RMAX;
-      qv[i] = (idx < CMAX * RMAX && c0 < m && j < r) ? st->Q[idx] : 0.0;
+      qv[i] = st->Q[min(idx, CMAX * RMAX - 1)];   // masked below: no wait for r and m first
     }
+    if constexpr (GENERAL) {
 #pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      const int idx = tid + i * CORE_THREADS;
-      const int j = idx % RMAX, k = idx / RMAX;
-      cv[i] = (j < r && k < r) ? st->C[idx] : 0.0;
+      for (int i = 0; i < NC; ++i) cv[i] = st->C[tid + i * CORE_THREADS];
     }
     load_records(0);
     // the small state the later steps read, fetched with the rest: sigma
@@ -929,10 +948,16 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const int idx = tid + i * CORE_THREADS;
-      if (idx < CMAX * RMAX) sQ[idx / RMAX * LDQ + idx % RMAX] = qv[i];
+      const int c0 = idx / RMAX, j = idx % RMAX;
+      if (idx < CMAX * RMAX) sQ[c0 * LDQ + j] = c0 < m && j < r ? qv[i] : 0.0;
     }
+    if constexpr (GENERAL) {
 #pragma unroll
-    for (int i = 0; i < NC; ++i) sC[tid + i * CORE_THREADS] = cv[i];
+      for (int i = 0; i < NC; ++i) {
+        const int idx = tid + i * CORE_THREADS;
+        sC[idx] = idx % RMAX < r && idx / RMAX < r ? cv[i] : 0.0;
+      }
+    }
   }
   if (tid < RMAX) sw[tid] = tid < r ? st->w[tid] : 0.0;
   {
@@ -961,31 +986,59 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   if constexpr (GENERAL) {
     const DevState* __restrict__ tst = c.tst;
     const int mT = tst->m;
-    constexpr int NSL = CORE_THREADS / CMAX;
-    double* part = sV;                       // scratch, as in step 1
-    if (tid < NSL * CMAX) {
-      const int it = tid % CMAX, sl = tid / CMAX;
-      double t = 0.0;
-      if (it < mT) {
-#pragma unroll 16
-        for (int b = sl; b < c.nblk; b += NSL) t += c.pt[(int64_t)b * PW + c.rbt + it];
+    constexpr int NSL = CORE_THREADS / CMAX, TU = 10;
+    constexpr int NQ = (CMAX * RMAX + CORE_THREADS - 1) / CORE_THREADS;
+    constexpr int NR = (CMAX + 15) / 16;
+    // sAV is scratch until the SVD: R in front, the partial sums behind it
+    double* sR = sAV;
+    double* part = sAV + CMAX * LDQ;
+    static_assert(CMAX * LDQ + NSL * CMAX <= 2 * MMAX * LDK, "R and the partial sums fit");
+    const int it = tid % CMAX, sl = tid / CMAX, j = tid >> 4, jl = tid & 15;
+    double tv[TU], rr[NQ], t = 0.0;
+    auto load_t = [&](int ch) {
+#pragma unroll
+      for (int i = 0; i < TU; ++i) {
+        if ((ch * TU + i) * NSL >= c.nblk) break;   // uniform
+        const int b = sl + (ch * TU + i) * NSL;
+        tv[i] = c.pt[(int64_t)(b < c.nblk ? b : 0) * PW + c.rbt + min(it, mT)];
       }
-      part[sl * CMAX + it] = t;
+    };
+    auto add_t = [&](int ch) {
+#pragma unroll
+      for (int i = 0; i < TU; ++i)
+        if (sl + (ch * TU + i) * NSL < c.nblk) t += tv[i];
+    };
+    load_t(0);
+    // R with them, to LDS in whole lines
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) rr[i] = tst->Q[min(tid + i * CORE_THREADS, CMAX * RMAX - 1)];
+    add_t(0);
+    for (int ch = 1; ch * TU * NSL < c.nblk; ++ch) {   // uniform
+      load_t(ch);
+      add_t(ch);
+    }
+    if (tid < NSL * CMAX) part[sl * CMAX + it] = it < mT ? t : 0.0;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int idx = tid + i * CORE_THREADS, c0 = idx / RMAX, k = idx % RMAX;
+      if (idx < CMAX * RMAX) sR[c0 * LDQ + k] = c0 < mT && k < r ? rr[i] : 0.0;
     }
     __syncthreads();
     if (tid < CMAX) {
-      double t = 0.0;
-      for (int sl = 0; sl < NSL; ++sl) t += part[sl * CMAX + tid];
-      red[tid] = t;
+      double u = 0.0;
+#pragma unroll
+      for (int w = 0; w < NSL; ++w) u += part[w * CMAX + tid];
+      red[tid] = u;
     }
     __syncthreads();
-    if (tid < RMAX) {
-      double t = 0.0;
-      if (tid < r)
-#pragma unroll 24
-        for (int c0 = 0; c0 < mT; ++c0) t += tst->Q[c0 * RMAX + tid] * red[c0];
-      eB[tid] = t;
+    double eb = 0.0;
+#pragma unroll
+    for (int h = 0; h < NR; ++h) {
+      const int c0 = min(jl + 16 * h, CMAX - 1);   // (row CMAX - 1 once more: not counted)
+      eb = __builtin_fma(jl + 16 * h < CMAX ? sR[c0 * LDQ + j] : 0.0, red[c0], eb);
     }
+    eb = row_sum(eb);
+    if (jl == 0) eB[j] = eb;
     __syncthreads();
   }
 
@@ -997,9 +1050,13 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
     const int j = tid >> 4, jl = tid & 15;
     if (j < r) {
       double a2 = 0.0, b2 = 0.0;
-      for (int c0 = jl; c0 < m; c0 += 16) {
-        a2 = __builtin_fma(sQ[c0 * LDQ + j], tot[P_SUE + c0], a2);
-        b2 = __builtin_fma(sQ[c0 * LDQ + j], tot[P_SUY + c0], b2);
+#pragma unroll
+      for (int h = 0; h < (CMAX + 15) / 16; ++h) {
+        const int c0 = min(jl + 16 * h, CMAX - 1);
+        const bool in = jl + 16 * h < m;
+        const double qv = sQ[c0 * LDQ + j], ue = tot[P_SUE + c0], uy = tot[P_SUY + c0];
+        a2 = __builtin_fma(qv, in ? ue : 0.0, a2);
+        b2 = __builtin_fma(qv, in ? uy : 0.0, b2);
       }
       a2 = row_sum(a2);
       b2 = row_sum(b2);
@@ -1036,8 +1093,12 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
     const int q0 = (tid - 128) >> 4, l16 = tid & 15;
     for (int row = q0; row < CMAX; row += (CORE_THREADS - 128) / 16) {
       double t = 0.0;
-      if (row < m || refolded)
-        for (int j = l16; j < r; j += 16) t += sQ[row * LDQ + j] * p2[j];
+#pragma unroll
+      for (int h = 0; h < RMAX / 16; ++h) {
+        const int j = l16 + 16 * h;
+        const double qv = sQ[row * LDQ + j], pv = p2[j];
+        t = __builtin_fma(qv, j < r ? pv : 0.0, t);
+      }
       t = row_sum(t);
       if (l16 == 0) red[row] = t;
     }
@@ -1117,10 +1178,33 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   // G(i, j) at sC[j * RMAX + i]), from the stored residual e = x - U p1
   // itself (no cancellation between x^T B and p^T G); zero when no
   // direction is added
-  if (GENERAL && tid < r) {
+  if constexpr (GENERAL) {
+    const int j = tid >> 4, jl = tid & 15;   // one quarter-wave per entry
     double t = 0.0;
-    for (int i = 0; i < r; ++i) t += p2[i] * sC[tid * RMAX + i];
-    qB[tid] = si[1] ? (eB[tid] - t) / sc[0] : 0.0;
+#pragma unroll
+    for (int h = 0; h < RMAX / 16; ++h) {
+      const int i = jl + 16 * h;
+      const double pv = p2[i], cv = sC[j * RMAX + i];
+      t = __builtin_fma(i < r ? pv : 0.0, cv, t);
+    }
+    t = row_sum(t);
+    if (jl == 0 && j < r) qB[j] = si[1] ? (eB[j] - t) / sc[0] : 0.0;
+  }
+
+  // (chained pairs: C to LDS by the wavefronts that the set-up below leaves
+  // idle; it is read from step 9 on, some barriers later)
+  if constexpr (!GENERAL) {
+    constexpr int NC = (RMAX * RMAX + CORE_THREADS - 65) / (CORE_THREADS - 64);
+    if (tid >= 64) {
+      double cv[NC];
+#pragma unroll
+      for (int i = 0; i < NC; ++i) cv[i] = st->C[min(tid - 64 + i * (CORE_THREADS - 64), RMAX * RMAX - 1)];
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const int idx = tid - 64 + i * (CORE_THREADS - 64);
+        if (idx < RMAX * RMAX) sC[idx] = idx % RMAX < r && idx / RMAX < r ? cv[i] : 0.0;
+      }
+    }
   }
 
   // 5. SVD of the core: secular equation, one-sided Jacobi if that fails
@@ -1163,16 +1247,27 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
     }
     __syncthreads();
   }
-  for (int col = tid >> 4; col < M; col += CORE_THREADS / 16) {
+  if ((tid >> 3) < M) {                    // eight lanes per column
+    const int col = tid >> 3, l8 = tid & 7;
     const double me = sd[col];
-    double rank = 0.0;
-    for (int k = qcl; k < M; k += 16) rank += (sd[k] > me || (sd[k] == me && k < col)) ? 1.0 : 0.0;
-    rank = row_sum(rank);
-    if (qcl == 0) perm[(int)rank] = col;
+    int rank = 0;
+#pragma unroll
+    for (int h = 0; h < SEC_TERMS; ++h) {
+      const int k = l8 + 8 * h;
+      const double sk = sd[min(k, M - 1)];
+      rank += (k < M) & ((sk > me) | ((sk == me) & (k < col)));
+    }
+    rank = oct_sum(rank);
+    if (l8 == 0) perm[rank] = col;
   }
   __syncthreads();
+  // columns kept: those above the tolerance (each wavefront counts them by itself)
   const double smax = sd[perm[0]];
-  const int above = __syncthreads_count(tid < M && smax > 0.0 && sd[tid] > sc[4] * smax);
+  const int l64 = tid & 63;
+  const double cut = sc[4] * smax;
+  const int above = smax > 0.0 ? __popcll(__ballot(l64 < M && sd[min(l64, M - 1)] > cut)) +
+                                     __popcll(__ballot(l64 + 64 < M && sd[min(l64 + 64, M - 1)] > cut))
+                               : 0;
   const int rn = min(above, c.r_max);
   if (rn == 0) {   // nothing kept (zero snapshots so far)
     if (tid < CMAX) st->a[tid] = 0.0;
@@ -1204,7 +1299,12 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
     if (k < rn) {
       const int pj = perm[k];
       double s = 0.0;
-      for (int i = kl; i < r; i += 16) s = __builtin_fma(sA[pj * LDK + i], pyr[i], s);
+#pragma unroll
+      for (int h = 0; h < RMAX / 16; ++h) {
+        const int i = max(min(kl + 16 * h, r - 1), 0);
+        const double av = sA[pj * LDK + i], yv = pyr[i];
+        s = __builtin_fma(av, kl + 16 * h < r ? yv : 0.0, s);
+      }
       s = row_sum(s);
       if (kl == 0) {
         const double inv = 1.0 / sd[pj];
@@ -1233,17 +1333,22 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   // it; (Q p2)[c] is in red since step 3): one 16-lane quarter-wave per entry
   const int qw = tid >> 4, ql = tid & 15;
   {
-    double bs = 0.0;                       // g . p_y up to 1/rho: U_k(r, :) p_y
-    for (int k = ql; k < rn; k += 16) bs += urk[k] * pyn[k];
-    const double bsum = row_sum(bs);
-    for (int j = qw; j < RMAX; j += CORE_THREADS / 16) {
+    static_assert(CORE_THREADS / 16 == RMAX, "one quarter-wave per entry");
+    double bs = 0.0, t = 0.0;              // bs: g . p_y up to 1/rho: U_k(r, :) p_y
+    const int j = max(min(qw, r - 1), 0);
+#pragma unroll
+    for (int h = 0; h < RMAX / 16; ++h) {
       // (G p_y)_j = sum_k U_k(j,k) p_y,k - (p2_j / rho) sum_k U_k(r,k) p_y,k
-      double t = 0.0;
-      if (j < r)
-        for (int k = ql; k < rn; k += 16) t += sA[perm[k] * LDK + j] * wk[k];
-      t = row_sum(t);
-      if (ql == 0) pvec[j] = j < r ? t - p2[j] * irho * bsum : 0.0;
+      const int k = min(ql + 16 * h, rn - 1);
+      const bool in = ql + 16 * h < rn;
+      const double uk = urk[k], yk = pyn[k], ak = sA[perm[k] * LDK + j], vk = wk[k];
+      bs = __builtin_fma(uk, in ? yk : 0.0, bs);
+      t = __builtin_fma(ak, in ? vk : 0.0, t);
     }
+    const double bsum = row_sum(bs);
+    t = row_sum(t);
+    // (the last thread entries past r: zero, read by the sums below)
+    if (ql == 0) pvec[qw] = qw < r ? t - p2[qw] * irho * bsum : 0.0;
   }
   __syncthreads();
   // Q' tiles: 16 x 16 blocks over the rows < mnew and the columns < r'
@@ -1263,7 +1368,7 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
         const int c0 = 16 * (tile / ncb), k0 = 16 * (tile % ncb);
         const int kb = k0 + (l & 15), ca = c0 + (l & 15);
         const int pk = kb < rn ? perm[kb] : 0;
-        d = mfma_tile(sQ + (ca < CMAX ? ca : 0) * LDQ, 1, ca < CMAX, sA + pk * LDK, 1, kb < rn, r, l);
+        d = mfma_tile(sQ + (ca < CMAX ? ca : 0) * LDQ, 1, sA + pk * LDK, 1, r, l);
         // element v of lane l: row c0 + 4 v + l/16, column k0 + l%16
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -1291,15 +1396,20 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
     const bool mine = idle > 0 ? wv >= ntile : true;
     const int q0 = idle > 0 ? qw - 4 * ntile : qw, nq = idle > 0 ? 4 * idle : CORE_THREADS / 16;
     if (mine) {
+      // rows < meff: pvec is zero and Q's columns are past r (r <= 0: no term)
+#pragma unroll 2
       for (int row = q0; row < CMAX; row += nq) {
+        const bool rest = row < meff, last = row == meff && grow;
         double t = 0.0;
-        if (row < meff) {
-          for (int j = ql; j < r; j += 16) t += sQ[row * LDQ + j] * pvec[j];
-        } else if (row == meff && grow) {
-          for (int k = ql; k < rn; k += 16) t += urk[k] * pyn[k];
+#pragma unroll
+        for (int h = 0; h < RMAX / 16; ++h) {
+          const int j = ql + 16 * h, k = min(j, rn - 1);
+          const double qv = sQ[row * LDQ + j], gv = pvec[j], uk = urk[k], yk = pyn[k];
+          const double x = rest ? qv : uk, y = rest ? gv : (j < rn ? yk : 0.0);
+          t = __builtin_fma(x, y, t);
         }
         t = row_sum(t);
-        if (ql == 0) st->a[row] = row == meff && grow ? t * irho : t;
+        if (ql == 0) st->a[row] = rest ? t : (last ? t * irho : 0.0);
       }
     }
   }
@@ -1323,7 +1433,7 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   }
 
   if constexpr (GENERAL) {
-    general_tail(c, r, rn, M, qy, sA, sV, sC, sQ, sd, sgn, pyr, qB, perm);
+    general_tail(c, r, rn, M, qy, sA, sV, sC, sQ, sgn, pyr, qB, perm);
   } else {
   // 9. T = E V_k[:, kept] with E = [[C, 0], [w^T, 0]] (M x r, the zero
   //    last column dropped), on the matrix cores: 16 x 16 tiles of T, K = r,
@@ -1336,8 +1446,7 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
       const int ia = i0 + (l & 15), bb = b0 + (l & 15);
       const int pb = bb < rn ? perm[bb] : 0;
       // row ia of E: row ia of C (stride RMAX along j) or w
-      const d4_t d = mfma_tile(ia < r ? sC + ia : sw, ia < r ? RMAX : 1, ia <= r, sV + pb * LDK, 1,
-                               bb < rn, r, l);
+      const d4_t d = mfma_tile(ia < r ? sC + ia : sw, ia < r ? RMAX : 1, sV + pb * LDK, 1, r, l);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int i = i0 + 4 * v + (l >> 4);
@@ -1360,8 +1469,7 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
       const int i0 = 16 * (tile % nt), j0 = 16 * (tile / nt);
       const int ia = i0 + (l & 15), jb = j0 + (l & 15);
       const int pa = ia < rn ? perm[ia] : 0;
-      const d4_t d = mfma_tile(sA + (jb < rn ? jb : 0) * LDK, 1, jb < rn, sV + pa * LDK, 1, ia < rn,
-                               M, l);
+      const d4_t d = mfma_tile(sA + (jb < rn ? jb : 0) * LDK, 1, sV + pa * LDK, 1, M, l);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int j = j0 + 4 * v + (l >> 4);
@@ -1431,55 +1539,67 @@ hipError_t launch_core(const CoreArgs& c, hipStream_t s, hipEvent_t e0, hipEvent
 __global__ __launch_bounds__(CORE_THREADS) void k_coef(CoefArgs c) {
   DevState* __restrict__ st = c.st;
   constexpr int NSL = CORE_THREADS / CMAX;   // partial-sum slots per column
+  constexpr int NQ = (CMAX * RMAX + CORE_THREADS - 1) / CORE_THREADS, TU = 20;
   __shared__ double part[NSL][CMAX];
   __shared__ double v[CMAX];
   __shared__ double p1[RMAX];
-  __shared__ double sQ[CMAX * RMAX];
+  __shared__ double sQ[CMAX * LDQ];
   const int tid = threadIdx.x;
+  // Q and the first TU records of each slot, all of a thread's loads issued
+  // together and before r and m are known
+  const int it = tid % CMAX, sl = tid / CMAX;
+  double qv[NQ], tv[TU], t = 0.0;
+  auto load_t = [&](int ch) {
+#pragma unroll
+    for (int i = 0; i < TU; ++i) {
+      if ((ch * TU + i) * NSL >= c.nblk) break;   // uniform
+      const int b = sl + (ch * TU + i) * NSL;
+      tv[i] = c.pproj[(int64_t)(b < c.nblk ? b : 0) * PW + it];
+    }
+  };
+  auto add_t = [&](int ch) {
+#pragma unroll
+    for (int i = 0; i < TU; ++i)
+      if (sl + (ch * TU + i) * NSL < c.nblk) t += tv[i];
+  };
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) qv[i] = st->Q[min(tid + i * CORE_THREADS, CMAX * RMAX - 1)];
+  load_t(0);
   const int r = st->r, m = st->m;
-  // Q to LDS (all of a thread's loads issued together), record sums with
-  // the loads of a slot overlapped
-  {
-    constexpr int NQ = (CMAX * RMAX + CORE_THREADS - 1) / CORE_THREADS;
-    double qv[NQ];
 #pragma unroll
-    for (int i = 0; i < NQ; ++i) {
-      const int idx = tid + i * CORE_THREADS;
-      qv[i] = (idx < CMAX * RMAX && idx / RMAX < m && idx % RMAX < r) ? st->Q[idx] : 0.0;
-    }
-#pragma unroll
-    for (int i = 0; i < NQ; ++i)
-      if (tid + i * CORE_THREADS < CMAX * RMAX) sQ[tid + i * CORE_THREADS] = qv[i];
+  for (int i = 0; i < NQ; ++i) {
+    const int idx = tid + i * CORE_THREADS, c0 = idx / RMAX, j = idx % RMAX;
+    if (idx < CMAX * RMAX) sQ[c0 * LDQ + j] = c0 < m && j < r ? qv[i] : 0.0;
   }
-  if (tid < NSL * CMAX) {
-    const int it = tid % CMAX, sl = tid / CMAX;
-    double t = 0.0;
-    if (it < m) {
-#pragma unroll 16
-      for (int b = sl; b < c.nblk; b += NSL) t += c.pproj[(int64_t)b * PW + it];
-    }
-    part[sl][it] = t;
+  add_t(0);
+  for (int ch = 1; ch * TU * NSL < c.nblk; ++ch) {   // uniform
+    load_t(ch);
+    add_t(ch);
   }
+  if (sl < NSL) part[sl][it] = it < m ? t : 0.0;
   __syncthreads();
   if (tid < CMAX) {
-    double t = 0.0;
-    for (int sl = 0; sl < NSL; ++sl) t += part[sl][tid];
-    v[tid] = t;
+    double u = 0.0;
+#pragma unroll
+    for (int w = 0; w < NSL; ++w) u += part[w][tid];
+    v[tid] = u;
   }
   __syncthreads();
+  // p1 = Q^T v and a = Q p1, one thread per entry, the terms in order (Q is
+  // zero past r and m)
   if (tid < RMAX) {
     double a1 = 0.0;
-    if (tid < r)
-      for (int c0 = 0; c0 < m; ++c0) a1 += sQ[c0 * RMAX + tid] * v[c0];
+#pragma unroll
+    for (int c0 = 0; c0 < CMAX; ++c0) a1 += sQ[c0 * LDQ + tid] * v[c0];
     p1[tid] = a1;
     st->p1[tid] = a1;
   }
   __syncthreads();
   if (tid < CMAX) {
-    double t = 0.0;
-    if (tid < m)
-      for (int j = 0; j < r; ++j) t += sQ[tid * RMAX + j] * p1[j];
-    st->a[tid] = t;
+    double u = 0.0;
+#pragma unroll
+    for (int j = 0; j < RMAX; ++j) u += sQ[tid * LDQ + j] * p1[j];
+    st->a[tid] = u;
   }
 }
 

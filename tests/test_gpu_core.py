@@ -1,0 +1,55 @@
+"""The small-state kernel at the edges of its straight-line forms: term slots
+per lane of the secular solver (3, 6 or 9 for up to 24, 48 or 65 poles), tile
+counts of its products, and the chunks in which it reads the passes' records.
+
+Inputs: Gaussian snapshots, so every update has the full rank cap and all its
+poles live.  Their singular values lie within a factor of ten of each other
+and an update perturbs them by a few units of FP64 rounding of the largest,
+so after at most 80 updates they agree with the oracle's to 1e-11 and one
+predicted state to 1e-9, the bounds of the other FP64 comparisons.
+"""
+import numpy as np
+import pytest
+
+from oracle import odmd_oracle as O
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_2311_18715_amd.odmd import ODMD
+
+
+def run_against_the_oracle(n, r_max, updates, pairs, seed, shape=None):
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((n, updates + 1))
+    Y = rng.standard_normal((n, updates)) if pairs == "general" else X[:, 1:]
+    g = ODMD(n, r_max, 1e-10, pairs=pairs, shape=shape)
+    o = (O.OnlineDMDF1 if pairs == "general" else O.OnlineDMD)(n, r_max, 1e-10)
+    Xd = torch.from_numpy(np.ascontiguousarray(X.T)).cuda()
+    Yd = torch.from_numpy(np.ascontiguousarray(Y.T)).cuda()
+    for j in range(updates):
+        g.update(Xd[j], Yd[j])
+        o.update(X[:, j], Y[:, j])
+    s = g.state()
+    assert s["r"] == o.r == min(r_max, updates)
+    assert g.info().last_sweeps == 0        # the secular solver found every root
+    np.testing.assert_allclose(s["sigma"], o.sigma, rtol=1e-11)
+    ref = np.asarray(o.predict(1)).reshape(-1)
+    got = g.predict(1).double().cpu().numpy().reshape(-1)
+    assert np.linalg.norm(got - ref) <= 1e-9 * np.linalg.norm(ref)
+    return g
+
+
+@pytest.mark.parametrize("pairs", ["chained", "general"])
+@pytest.mark.parametrize("r_max", [1, 7, 15, 16, 23, 24, 25, 47, 48, 49, 63, 64])
+def test_every_rank_edge(r_max, pairs):
+    run_against_the_oracle(900, r_max, r_max + 14, pairs, 100 + r_max)
+
+
+@pytest.mark.parametrize("pairs", ["chained", "general"])
+@pytest.mark.parametrize("blocks", [1, 13, 14, 130, 131, 261])
+def test_record_chunks(blocks, pairs):
+    """One record per 16 rows here: 13 slots of records, read ten at a time."""
+    g = run_against_the_oracle(16 * blocks, 6, 24 if blocks > 1 else 12, pairs, 7 + blocks, (256, 16, 512))
+    assert g.info().nblocks == blocks
