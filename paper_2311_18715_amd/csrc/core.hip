@@ -175,7 +175,10 @@ __device__ __forceinline__ bool secular_vectors(double* A, double* V, int r, int
   // registers; dead slots hold a live pole with zero weight, so that no
   // step tests for them.  These steps are bound by the FP64 issue rate (the
   // scalar part of each root's iteration is repeated by its lanes), so
-  // fewer lanes per root and straight-line code count.
+  // fewer lanes per root and straight-line code count: the roots of r = 40
+  // took 18.6k cycles with sixteen lanes and a run-time term count (which
+  // made the compiler index registers) and take 11.6k, of r = 64 33.8k and
+  // 20k, of r = 20 11.7k and 5.5k.
   const int grp = tid >> 3, gl = tid & 7;
   double tdj[NT], tzz[NT];
 #pragma unroll
@@ -459,8 +462,8 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
   __syncthreads();
   const int nd = S.nd;
 
-  // (straight-line code for the term slots in use: a run-time count made the
-  // compiler index registers)
+  // (three forms of straight-line code: a form per slot count would be three
+  // times the code for at most two dead slots)
   bool ok;
   if (nd <= 24) ok = secular_vectors<3>(A, V, r, nd, S, sdo);
   else if (nd <= 48) ok = secular_vectors<6>(A, V, r, nd, S, sdo);
@@ -515,7 +518,10 @@ typedef double d4_t __attribute__((ext_vector_type(4)));
 // pointer: what it reads reaches only elements of D out of range, which the
 // callers drop.  Two accumulators over alternate k-steps keep two products
 // in flight, and the next eight k-steps' operands are loaded while these
-// are multiplied.
+// are multiplied.  Only the last eight k-steps test k against K and the
+// pointers step by sums: with the tests, clamps and integer products of
+// every load the vector unit, not the matrix cores (64 cycles a product),
+// was the bound (Q' and a of r = 64: 16.5k cycles, then 12k).
 struct TileOps {
   const double *a, *b;
   int sa, sb;
@@ -612,7 +618,10 @@ __device__ __forceinline__ d4_t mfma_tile(const double* pa, int sa, const double
 //     G' = U'^T B' = U_k^T E V_k,   E = [[G, U^T y], [q^T B, q^T y]],
 //     R' = [[R, 0], [0, 1]] V_k,    A~ = G' diag(sigma')^-1.
 // U_k(i, a) = sA[perm[a] * LDK + i] / sd[perm[a]], V_k(i, a) = sV[perm[a] *
-// LDK + i]; sQ is free here (Q' is written) and receives E V_k.
+// LDK + i]; sQ is free here (Q' is written) and holds R, then E V_k.  R comes
+// in whole lines through LDS: read as operands, 16 lanes in 16 rows, it was
+// the largest part of this phase (24k cycles in all at r = 40, 17k now; 41k
+// and 27k at r = 64).
 __device__ __forceinline__ void general_tail(const CoreArgs& c, int r, int rn, int M, double qy,
                                           const double* sA, const double* sV, const double* sC,
                                           double* sQ, const double* sgn, const double* pyr, const double* qB, const int* perm) {
