@@ -151,19 +151,6 @@ __device__ __forceinline__ double recip(double x) {
   return r;
 }
 
-// One Newton step (1e-15), and sqrt likewise from the reciprocal square root:
-// for the steps of the root iteration, which its tests check anyway.
-// recip1(0) is NaN.
-__device__ __forceinline__ double recip1(double x) {
-  const double r = __builtin_amdgcn_rcp(x);
-  return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
-}
-__device__ __forceinline__ double sqrt1(double x) {
-  const double y = __builtin_amdgcn_rsq(x), g = x * y;
-  const double s = __builtin_fma(g, __builtin_fma(-0.5 * y, g, 0.5), g);
-  return x > 0.0 ? s : 0.0;
-}
-
 // Roots, z~ and singular vectors of the nd live poles.  NT: the term slots
 // per lane, at least ceil(nd / 8).  False when a root was not found.
 template <int NT>
@@ -203,7 +190,7 @@ __device__ __forceinline__ bool secular_vectors(double* A, double* V, int r, int
       double fm = 0.0, zsum = 0.0;     // f at the middle of the gap; sum of z^2
 #pragma unroll
       for (int m = 0; m < NT; ++m) {
-        fm = __builtin_fma(tzz[m], recip1((tdj[m] - plo) * (tdj[m] + plo) - half), fm);
+        fm = __builtin_fma(tzz[m], recip((tdj[m] - plo) * (tdj[m] + plo) - half), fm);
         zsum += tzz[m];
       }
       fm = 1.0 + oct_sum(fm);
@@ -225,12 +212,14 @@ __device__ __forceinline__ bool secular_vectors(double* A, double* V, int r, int
         // taken when it falls inside the bracket (else the midpoint).  A root
         // far from the bracket's middle (a wide gap between the kept and the
         // dropped directions) then needs a few iterations instead of ~9.
+        // (to full precision: where two terms are all there is, the tests
+        // below take this root as it is)
         const double zK = low ? zlo : zhi, del = low ? dhi : dlo;
-        const double qa = __builtin_fma(zlo - zhi, recip1(half), fm);
+        const double qa = fm + (zlo - zhi) / half;
         const double qb = -(qa * del + zlo + zhi), qc = zK * del;
         const double disc = qb * qb - 4.0 * qa * qc;
-        const double qq = -0.5 * (qb + __builtin_copysign(sqrt1(disc), qb));
-        const double g1 = qq * recip1(qa), g2 = qc * recip1(qq);
+        const double qq = -0.5 * (qb + __builtin_copysign(sqrt(disc), qb));
+        const double g1 = qq / qa, g2 = qc / qq;
         const bool guess = i > 0 && disc >= 0.0;
         const bool in1 = g1 > lo && g1 < hi, in2 = g2 > lo && g2 < hi;
         mu = guess && (in1 || in2) ? (in1 ? g1 : g2) : mu;
@@ -265,14 +254,15 @@ __device__ __forceinline__ bool secular_vectors(double* A, double* V, int r, int
             (hi - lo <= 4.0 * SEC_EPS * fmax(fabs(lo), fabs(hi))))
           break;
         // (the step only steers the iteration; the tests above decide
-        // convergence.  cq = 0 leaves r2, which is then the linear root)
+        // convergence, so reciprocals stand in for the divisions.  cq = 0
+        // leaves r2, which is then the linear root)
         const double Dlo = dlo - mu, Dhi = dhi - mu, dw = dpsi + dphi, DD = Dlo * Dhi;
         const double cq = w - Dlo * dpsi - Dhi * dphi;
         const double aq = (Dlo + Dhi) * w - DD * dw;
         const double bq = DD * w;
-        const double disc = sqrt1(fabs(aq * aq - 4.0 * bq * cq));
+        const double disc = sqrt(fabs(aq * aq - 4.0 * bq * cq));
         const double qv = 0.5 * (aq + __builtin_copysign(disc, aq));
-        const double r1 = qv * recip1(cq), r2 = bq * recip1(qv), rn = -w * recip1(dw);
+        const double r1 = qv * recip(cq), r2 = bq * recip(qv), rn = -w * recip(dw);
         const double l1 = elo - mu, l2 = ehi - mu;
         const bool v1 = (r1 > l1) & (r1 < l2), v2 = (r2 > l1) & (r2 < l2);
         double eta = v1 ? r1 : r2;
