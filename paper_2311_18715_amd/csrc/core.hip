@@ -72,10 +72,24 @@ __device__ __forceinline__ int jacobi_sweeps(double* A, double* V, double* d, in
         int a, b;
         rr_pair(round, pi, Mp, a, b);
         if (b >= M) continue;
+        // both pairs of columns are read at once, straight-line, and rotated
+        // from registers (the rounds are a chain of latencies)
+        constexpr int NR = (MMAX + 31) / 32;
+        double xa[NR], xb[NR], va[NR], vb[NR];
         double g = 0.0;
-        for (int row = hl; row < M; row += 32) g += A[a * LDK + row] * A[b * LDK + row];
-        g = halfwave_sum(g);
+#pragma unroll
+        for (int h = 0; h < NR; ++h) {
+          const int row = min(hl + 32 * h, M - 1);
+          xa[h] = A[a * LDK + row];
+          xb[h] = A[b * LDK + row];
+          va[h] = V[a * LDK + row];
+          vb[h] = V[b * LDK + row];
+        }
         const double al = d[a], be = d[b];
+#pragma unroll
+        for (int h = 0; h < NR; ++h)
+          if (hl + 32 * h < M) g += xa[h] * xb[h];
+        g = halfwave_sum(g);
         if (fmin(al, be) > dfloor && fabs(g) > tolJ * sqrt(al * be)) {
           const double zeta = (be - al) / (2.0 * g);
           const double az = fabs(zeta);
@@ -83,13 +97,15 @@ __device__ __forceinline__ int jacobi_sweeps(double* A, double* V, double* d, in
           if (zeta < 0.0) t = -t;
           const double c = 1.0 / sqrt(1.0 + t * t);
           const double s = c * t;
-          for (int row = hl; row < M; row += 32) {
-            const double xa = A[a * LDK + row], xb = A[b * LDK + row];
-            A[a * LDK + row] = c * xa - s * xb;
-            A[b * LDK + row] = s * xa + c * xb;
-            const double va = V[a * LDK + row], vb = V[b * LDK + row];
-            V[a * LDK + row] = c * va - s * vb;
-            V[b * LDK + row] = s * va + c * vb;
+#pragma unroll
+          for (int h = 0; h < NR; ++h) {
+            const int row = hl + 32 * h;
+            if (row < M) {
+              A[a * LDK + row] = c * xa[h] - s * xb[h];
+              A[b * LDK + row] = s * xa[h] + c * xb[h];
+              V[a * LDK + row] = c * va[h] - s * vb[h];
+              V[b * LDK + row] = s * va[h] + c * vb[h];
+            }
           }
           if (hl == 0) {
             d[a] = al - t * g;
@@ -164,8 +180,8 @@ __device__ __forceinline__ bool secular_vectors(double* A, double* V, int r, int
   // scalar part of each root's iteration is repeated by its lanes), so
   // fewer lanes per root and straight-line code count: the roots of r = 40
   // took 18.6k cycles with sixteen lanes and a run-time term count (which
-  // made the compiler index registers) and take 11.6k, of r = 64 33.8k and
-  // 20k, of r = 20 11.7k and 5.5k.
+  // made the compiler index registers) and take 12.3k, of r = 64 33.8k and
+  // 21k, of r = 20 11.7k and 6.1k.
   const int grp = tid >> 3, gl = tid & 7;
   double tdj[NT], tzz[NT];
 #pragma unroll
@@ -769,7 +785,15 @@ __device__ void gram_fix(const CoreArgs& c, int r, double* sA, double* sV, doubl
     const int row = 16 * I + 4 * (ln >> 4) + v, col = 16 * J + (ln & 15);
     if (J < nb && row < r && col < r) {
       double t = 0.0;
-      for (int w = 0; w < c.gnwg; ++w) t += c.grec[(int64_t)w * GRAM_REC + e];
+      constexpr int WU = 16;                       // records in flight
+      for (int w0 = 0; w0 < c.gnwg; w0 += WU) {
+        double gv[WU];
+#pragma unroll
+        for (int i = 0; i < WU; ++i) gv[i] = c.grec[(int64_t)min(w0 + i, c.gnwg - 1) * GRAM_REC + e];
+#pragma unroll
+        for (int i = 0; i < WU; ++i)
+          if (w0 + i < c.gnwg) t += gv[i];
+      }
       sA[col * LDK + row] = t;
       if (I != J) sA[row * LDK + col] = t;
     }
@@ -1396,7 +1420,6 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
     const int q0 = idle > 0 ? qw - 4 * ntile : qw, nq = idle > 0 ? 4 * idle : CORE_THREADS / 16;
     if (mine) {
       // rows < meff: pvec is zero and Q's columns are past r (r <= 0: no term)
-#pragma unroll 2
       for (int row = q0; row < CMAX; row += nq) {
         const bool rest = row < meff, last = row == meff && grow;
         double t = 0.0;

@@ -12,9 +12,9 @@
 // Layout: S' in 64-row tiles, column-major inside a tile, so four
 // consecutive rows of a column are 8 contiguous bytes: exactly the operand
 // of one lane of the 16x16x16 BF16 matrix-core product, which contracts over
-// 16 rows.  A wavefront takes 16 rows of one tile (a unit) and, for every
-// pair of 16-column blocks I <= J, adds S'_I^T S'_J of those rows (lane l
-// supplies rows 4 (l/16) .. 4 (l/16) + 3 of column 16 I + l%16 for both
+// 16 rows.  A wavefront takes a tile and, 16 rows (a unit) at a time and for
+// every pair of 16-column blocks I <= J, adds S'_I^T S'_J of those rows (lane
+// l supplies rows 4 (l/16) .. 4 (l/16) + 3 of column 16 I + l%16 for both
 // operands); the FP32 block sums of a unit are added into FP64 accumulators.
 // A workgroup sums its waves in a fixed order and writes one record per
 // workgroup; the small-state kernel adds the records in index order, so the
@@ -29,9 +29,11 @@
 namespace odmd {
 
 typedef short s4_t __attribute__((ext_vector_type(4)));
+typedef short h8_t __attribute__((ext_vector_type(8)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
 constexpr int GRAM_THREADS = 512;
+constexpr int GRAM_LD = 72;     // rows of a column in LDS: 64 and padding
 
 __device__ __forceinline__ void gram_body(const GramArgs& g, int wg) {
   const DevState* __restrict__ st = g.st;
@@ -48,33 +50,59 @@ __device__ __forceinline__ void gram_body(const GramArgs& g, int wg) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) acc[p][v] = 0.0;
 
-  const int64_t units = (g.n + 15) / 16;
-  const int64_t u0 = (int64_t)wg * units / g.nwg, u1 = (int64_t)(wg + 1) * units / g.nwg;
+  const int64_t tiles = (g.n + 63) / 64;
+  const int64_t t0 = (int64_t)wg * tiles / g.nwg, t1 = (int64_t)(wg + 1) * tiles / g.nwg;
   const uint16_t* __restrict__ Us = static_cast<const uint16_t*>(g.Us);
-  for (int64_t u = u0 + wave; u < u1; u += NW) {
-    // rows of the last tile past n are zero (never written)
-    const uint16_t* T = Us + (u >> 2) * (int64_t)g.ct * 64 + 16 * (u & 3) + 4 * q;
-    s4_t op[GRAM_BLOCKS];
+  // The operands of a load would be 32 bytes of 16 lines, and the lines, not
+  // the bytes, are what a load costs (about five cycles each: 731 us at
+  // n = 6M, r = 64 on 64 compute units).  A tile's columns are contiguous,
+  // so a wave reads its tile 1 KB a load and turns it in LDS of its own,
+  // columns GRAM_LD apart (reads of 16 columns fall in distinct banks).
+  __shared__ __attribute__((aligned(16))) uint16_t smem[NW * 16 * GRAM_BLOCKS * GRAM_LD];
+  static_assert(sizeof(smem) >= GRAM_REC * sizeof(double), "the record takes the tiles' place");
+  uint16_t* sw = smem + wave * 16 * GRAM_BLOCKS * GRAM_LD;
+  // columns 8 i + lane / 8, rows 8 (lane % 8) .. + 7 (the rows of the last
+  // tile past n are zero, never written); columns past the blocks in use
+  // re-read the first ones and are not used
+  constexpr int NL = 2 * GRAM_BLOCKS;
+  auto load_tile = [&](int64_t t, h8_t (&v)[NL]) {
+    const uint16_t* T = Us + t * (int64_t)g.ct * 64 + 8 * lane;
 #pragma unroll
-    for (int I = 0; I < GRAM_BLOCKS; ++I)
-      op[I] = I < nb ? *reinterpret_cast<const s4_t*>(T + (16 * I + l16) * 64) : s4_t{0, 0, 0, 0};
-    int p = 0;
+    for (int i = 0; i < NL; ++i) v[i] = *reinterpret_cast<const h8_t*>(T + (i < 2 * nb ? i * 512 : 0));
+  };
+  h8_t next[NL];
+  int64_t t = t0 + wave;
+  if (t < t1) load_tile(t, next);
+  for (; t < t1; t += NW) {
 #pragma unroll
-    for (int I = 0; I < GRAM_BLOCKS; ++I)
+    for (int i = 0; i < NL; ++i)
+      *reinterpret_cast<h8_t*>(sw + (8 * i + (lane >> 3)) * GRAM_LD + 8 * (lane & 7)) = next[i];
+    load_tile(t + NW < t1 ? t + NW : t, next);   // under this tile's products
 #pragma unroll
-      for (int J = I; J < GRAM_BLOCKS; ++J, ++p) {
-        if (J < nb) {                        // uniform
-          const f4_t d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(op[I], op[J], f4_t{0.f, 0.f, 0.f, 0.f},
-                                                                  0, 0, 0);
+    for (int j = 0; j < 4; ++j) {            // sixteen rows at a time
+      s4_t op[GRAM_BLOCKS];
 #pragma unroll
-          for (int v = 0; v < 4; ++v) acc[p][v] += (double)d[v];
+      for (int I = 0; I < GRAM_BLOCKS; ++I)
+        op[I] = *reinterpret_cast<const s4_t*>(sw + (16 * I + l16) * GRAM_LD + 16 * j + 4 * q);
+      int p = 0;
+#pragma unroll
+      for (int I = 0; I < GRAM_BLOCKS; ++I)
+#pragma unroll
+        for (int J = I; J < GRAM_BLOCKS; ++J, ++p) {
+          if (J < nb) {                      // uniform
+            const f4_t d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(op[I], op[J], f4_t{0.f, 0.f, 0.f, 0.f},
+                                                                    0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[p][v] += (double)d[v];
+          }
         }
-      }
+    }
   }
   // waves in index order into one LDS record, then the record to memory:
   // entry p * 256 + 4 lane + v is the (4 (lane/16) + v, lane%16) element of
   // block pair p (I <= J, row-major over I then J)
-  __shared__ double red[GRAM_REC];
+  double* red = reinterpret_cast<double*>(smem);
+  __syncthreads();
   for (int w = 0; w < NW; ++w) {
     if (wave == w) {
 #pragma unroll

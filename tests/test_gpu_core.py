@@ -53,3 +53,25 @@ def test_record_chunks(blocks, pairs):
     """One record per 16 rows here: 13 slots of records, read ten at a time."""
     g = run_against_the_oracle(16 * blocks, 6, 24 if blocks > 1 else 12, pairs, 7 + blocks, (256, 16, 512))
     assert g.info().nblocks == blocks
+
+
+@pytest.mark.parametrize("r_max", [15, 16, 33, 64])
+@pytest.mark.parametrize("n", [700, 704, 8191, 8257, 16385])
+def test_bf16_refold_gram_edges(n, r_max):
+    """The Gram matrix of a rewritten BF16 basis with a ragged last tile, one,
+    two and three workgroups of 8192 rows and 1 to 4 blocks of 16 columns.
+    Rounded columns alone are off orthonormal by r 2^-9 / sqrt(n), at most
+    5e-3 here; rows left out or counted twice would show as their share of
+    the rows, at least 64 / 16385 per direction."""
+    rng = np.random.default_rng(n + r_max)
+    X = torch.from_numpy(rng.standard_normal((r_max + 40, n)).astype(np.float32)).cuda()
+    g = ODMD(n, r_max, 1e-8, basis="bf16")
+    stored = [0]
+    for j in range(len(X) - 1):
+        g.update(X[j], X[j + 1])
+        stored.append(g.info().stored)
+    assert any(b < a for a, b in zip(stored, stored[1:]))       # refolded
+    U = g.basis_matrix().double()
+    assert U.shape[1] == r_max
+    orth = torch.linalg.norm(U.T @ U - torch.eye(r_max, dtype=U.dtype, device=U.device), 2).item()
+    assert orth < (5e-3 if n < 8000 else 2e-3)
