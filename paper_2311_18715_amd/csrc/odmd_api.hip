@@ -284,6 +284,9 @@ odmd_status launch_update(odmd_t h, const void* x, const void* y) {
   p.threads = h->threads;
   p.rows2 = h->rows2;
   const int kb = live_bucket(h);
+  // (T's column count is not in the host's feedback: its sweep, and the pass
+  // beside it, take the capacity's bucket)
+  const int pass_kb = h->general ? h->ct : kb;
   if (h->general) {
     // U^T x from a projection sweep, then the coefficients of the streaming
     // pass (which also writes e contiguously for the T sweep below)
@@ -298,10 +301,10 @@ odmd_status launch_update(odmd_t h, const void* x, const void* y) {
     HIP_OK(launch_coef(ca, h->stream));
     p.eout = h->eout;
   }
-  HIP_OK(launch_pass(p, (int)h->basis, kb, h->stream, ev ? ev[0] : nullptr, ev && !lat ? ev[1] : nullptr));
+  const hipEvent_t e0 = ev ? ev[0] : nullptr, e1 = ev && !lat ? ev[1] : nullptr;
   if (h->general) {
-    // the T sweep: appends y to T (refolding T when it is full) with zero
-    // coefficients; its records carry T^T e
+    // with the T sweep: appends y to T (refolding T when it is full) with
+    // zero coefficients; its records carry T^T e
     PassArgs pt = p;
     pt.Us = h->Ts;
     pt.x = y;
@@ -309,7 +312,9 @@ odmd_status launch_update(odmd_t h, const void* x, const void* y) {
     pt.partials = h->pt;
     pt.st = h->tst;
     pt.eout = nullptr;
-    HIP_OK(launch_pass(pt, (int)h->basis, h->ct, h->stream));
+    HIP_OK(launch_pass_pair(p, pt, (int)h->basis, pass_kb, h->stream, e0, e1));
+  } else {
+    HIP_OK(launch_pass(p, (int)h->basis, pass_kb, h->stream, e0, e1));
   }
   if (h->grec) HIP_OK(launch_gram(gram_args(h), h->stream));
   h->seq = (h->seq + 1) & 0xFFFFFFu;
@@ -321,7 +326,7 @@ odmd_status launch_update(odmd_t h, const void* x, const void* y) {
   c.gnwg = h->gnwg;
   c.r_max = h->r_max;
   c.jacobi_only = h->jacobi_only;
-  c.rb = kb;
+  c.rb = pass_kb;
   c.ct = h->ct;
   c.fold_slack = fold_slack(h);
   c.fb = h->fb_dev;

@@ -29,6 +29,10 @@ struct PassArgs {
 // that take the kernel's own start and end timestamps.
 hipError_t launch_pass(const PassArgs& p, int basis, int rb, hipStream_t s,
                        hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+// General pairs: the pass p (p.eout set) and the T sweep t that reads its e,
+// in one launch of one bucket rb, for both sets of columns.
+hipError_t launch_pass_pair(const PassArgs& p, const PassArgs& t, int basis, int rb, hipStream_t s,
+                            hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // Projection-only sweep of a general pair (same records with e = x: S^T x,
 // S^T y, x.x, x.y, x.x, y.y; stores nothing, never refolds).
 hipError_t launch_proj(const PassArgs& p, int basis, int rb, hipStream_t s);
