@@ -245,7 +245,6 @@ __device__ __forceinline__ void combine32_body(const CombineArgs& c, const int b
 // (5.9 TB/s), BF16 782 -> 134 us (6.4 TB/s); FP64, which needs no
 // conversion and keeps the test (it skips the loads of a short bucket), 595 us
 // (5.8 TB/s).
-constexpr int CR_KMAX = 4;
 template <typename TS, typename TO, int RB>
 __device__ __forceinline__ void combine_rows_body(const CombineArgs& c, const int64_t blk) {
   typedef Storage<TS> SC;
@@ -303,6 +302,33 @@ __global__ __launch_bounds__(CB_THREADS) void k_combine(CombineArgs c) {
   combine_block<KIND, TS, TO, RB, NS, NT>(c, blockIdx.x, gridDim.x, blockIdx.y);
 }
 
+// A few states of many streams in one launch: workgroup b belongs to the
+// stream whose range from blk0 on holds b and does what workgroup b - blk0
+// of that stream's own launch does.  One state of each of 256 FP32 streams
+// of 1e4 to 1e6 rows: 4.4 ms with a launch each (8 us of reading and a start
+// and an end for each), 2.1 ms in one per bucket.
+template <typename TS, typename TO, int RB>
+__global__ __launch_bounds__(CB_THREADS) void k_combine_few(const CombineDesc* __restrict__ d, int nd) {
+  typedef const __attribute__((address_space(4))) CombineDesc* cdesc;
+  cdesc D = (cdesc)d;
+  const int b = blockIdx.x;
+  int lo = 0, hi = nd - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (D[mid].blk0 <= b) lo = mid;
+    else hi = mid - 1;
+  }
+  CombineArgs c{};
+  c.st = D[lo].c.st;
+  c.Us = D[lo].c.Us;
+  c.out = D[lo].c.out;
+  c.n = D[lo].c.n;
+  c.ldo = D[lo].c.ldo;
+  c.ct = D[lo].c.ct;
+  c.K = D[lo].c.K;
+  combine_rows_body<TS, TO, RB>(c, b - D[lo].blk0);
+}
+
 // Read-out class of a launch: the kernel and its states per workgroup.  A
 // few states are read bound (rows); FP32 states of FP32 or BF16 columns go to
 // the FP32 matrix cores in up to four 32-state blocks, the rest to the FP64
@@ -312,7 +338,7 @@ __global__ __launch_bounds__(CB_THREADS) void k_combine(CombineArgs c) {
 // chains and fewer re-reads of the stored columns.)
 struct CombineClass { int kind, ns, states; };   // states: per workgroup
 static CombineClass combine_class(int basis, int out_f32, int K) {
-  if (K <= CR_KMAX) return {KIND_ROWS, 1, K};
+  if (K <= COMBINE_FEW) return {KIND_ROWS, 1, K};
   if (out_f32 && basis != 0) {
     const int ns = std::min(4, (K + 31) / 32);
     return {KIND_FP32, ns, 32 * ns};
@@ -337,6 +363,11 @@ static int cu_count() {
   return cache[dev] = cus;
 }
 
+int combine_few_blocks(int64_t n, int basis) {
+  const int64_t rows = CB_THREADS * (basis == 0 ? 1 : (basis == 1 ? 2 : 4));
+  return (int)((n + rows - 1) / rows);
+}
+
 // Grid of one read-out.  Rows: one thread per 8 bytes of a column.  Else one
 // workgroup per CU in all (two with streaming stores; see the top of the
 // file), shared by the launch's state blocks, with a unit per wavefront at least.  Workgroups go to the
@@ -344,10 +375,7 @@ static int cu_count() {
 // state blocks of one row share run on the same XCD and read its stored
 // columns through one L2.
 static dim3 combine_grid(const CombineArgs& c, const CombineClass& k, int basis, bool nt) {
-  if (k.kind == KIND_ROWS) {
-    const int64_t rows = CB_THREADS * (basis == 0 ? 1 : (basis == 1 ? 2 : 4));
-    return dim3((unsigned)((c.n + rows - 1) / rows), 1);
-  }
+  if (k.kind == KIND_ROWS) return dim3((unsigned)combine_few_blocks(c.n, basis), 1);
   const int ur = (k.kind == KIND_FP32 ? 32 : 16) * (CB_THREADS / 64);
   const unsigned ys = (unsigned)((c.K + k.states - 1) / k.states);
   int64_t g = std::min<int64_t>((c.n + ur - 1) / ur, std::max<int64_t>(1, (nt ? 2 : 1) * cu_count() / (int64_t)ys));
@@ -404,6 +432,31 @@ hipError_t launch_combine(const CombineArgs& c, int basis, int out_f32, int rb, 
     case 3: return nt ? launch_t<float, float, true>(c, basis, 1, rb, s) : launch_t<float, float, false>(c, basis, 1, rb, s);
     case 4: return nt ? launch_t<bf16, double, true>(c, basis, 0, rb, s) : launch_t<bf16, double, false>(c, basis, 0, rb, s);
     case 5: return nt ? launch_t<bf16, float, true>(c, basis, 1, rb, s) : launch_t<bf16, float, false>(c, basis, 1, rb, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <typename TS, typename TO>
+static hipError_t launch_few(const CombineDesc* d, int nd, int nblocks, int rb, hipStream_t s) {
+  switch (rb) {
+#define ODMD_CASE(RB) \
+  case RB: hipLaunchKernelGGL((k_combine_few<TS, TO, RB>), dim3(nblocks), dim3(CB_THREADS), 0, s, d, nd); break;
+    ODMD_CASE(8) ODMD_CASE(16) ODMD_CASE(24) ODMD_CASE(32) ODMD_CASE(40) ODMD_CASE(48)
+    ODMD_CASE(56) ODMD_CASE(64) ODMD_CASE(72)
+#undef ODMD_CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_combine_few(const CombineDesc* d, int nd, int nblocks, int basis, int out_f32, int rb,
+                              hipStream_t s) {
+  switch (2 * basis + (out_f32 ? 1 : 0)) {   // (an FP64 basis has FP64 states)
+    case 0: return launch_few<double, double>(d, nd, nblocks, rb, s);
+    case 2: return launch_few<float, double>(d, nd, nblocks, rb, s);
+    case 3: return launch_few<float, float>(d, nd, nblocks, rb, s);
+    case 4: return launch_few<bf16, double>(d, nd, nblocks, rb, s);
+    case 5: return launch_few<bf16, float>(d, nd, nblocks, rb, s);
   }
   return hipErrorInvalidValue;
 }

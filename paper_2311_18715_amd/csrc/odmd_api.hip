@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -1096,9 +1097,21 @@ odmd_status odmd_predict_batch(odmd_t* hs, const int32_t* steps, void* const* ou
   {
     std::unique_lock<std::mutex> lk;
     BatchSlot* sl = nullptr;
-    // the states' table, then the first chunk's step counts
+    // the states' table, the first chunk's step counts, then the read-outs
+    // of the streams that want a few states, which share a launch per
+    // storage type and bucket (the others fill the chip one by one)
+    std::vector<int> few;
+    std::vector<int> kb(count);
+    for (int32_t i = 0; i < count; ++i) {
+      kb[i] = live_bucket(hs[i]);
+      if (steps[i] <= COMBINE_FEW) few.push_back(i);
+    }
+    auto key = [&](int i) { return std::make_tuple((int)hs[i]->basis, (int)hs[i]->io, kb[i]); };
+    std::sort(few.begin(), few.end(), [&](int a, int b) { return key(a) != key(b) ? key(a) < key(b) : a < b; });
     const size_t tb = round_up((int64_t)count * sizeof(DevState*), 16);
-    const odmd_status s = acquire_slot(hs[0]->device, tb + (size_t)count * sizeof(int), lk, sl);
+    const size_t cb = tb + round_up((int64_t)count * sizeof(int), 16);
+    const size_t bytes = cb + few.size() * sizeof(CombineDesc);
+    const odmd_status s = acquire_slot(hs[0]->device, bytes, lk, sl);
     if (s != ODMD_OK) return s;
     DevState** tab = static_cast<DevState**>(sl->host);
     int* ks = reinterpret_cast<int*>(static_cast<char*>(sl->host) + tb);
@@ -1106,15 +1119,41 @@ odmd_status odmd_predict_batch(odmd_t* hs, const int32_t* steps, void* const* ou
       tab[i] = hs[i]->st;
       ks[i] = std::min(coef_chunk(hs[i]->r_max), (int)steps[i]);
     }
-    HIP_OK(hipMemcpyAsync(sl->dev, sl->host, tb + (size_t)count * sizeof(int), hipMemcpyHostToDevice,
-                          hs[0]->stream));
+    CombineDesc* cd = reinterpret_cast<CombineDesc*>(static_cast<char*>(sl->host) + cb);
+    struct FewLaunch { int first, nd, nblocks; };
+    std::vector<FewLaunch> fl;
+    for (size_t k = 0; k < few.size(); ++k) {
+      odmd_t h = hs[few[k]];
+      const int blocks = combine_few_blocks(h->n, (int)h->basis);
+      if (k == 0 || key(few[k]) != key(few[k - 1]) || fl.back().nblocks > INT_MAX - blocks)
+        fl.push_back(FewLaunch{(int)k, 0, 0});
+      CombineDesc& d = cd[k];
+      d = CombineDesc{};
+      d.c.st = h->st;
+      d.c.Us = h->Us;
+      d.c.out = outs[few[k]];
+      d.c.n = d.c.ldo = h->n;
+      d.c.ct = h->ct;
+      d.c.K = steps[few[k]];
+      d.blk0 = fl.back().nblocks;
+      fl.back().nblocks += blocks;
+      ++fl.back().nd;
+    }
+    HIP_OK(hipMemcpyAsync(sl->dev, sl->host, bytes, hipMemcpyHostToDevice, hs[0]->stream));
     HIP_OK(launch_power_coef_batch(static_cast<DevState* const*>(sl->dev),
                                    reinterpret_cast<const int*>(static_cast<char*>(sl->dev) + tb), count,
                                    hs[0]->stream));
+    const CombineDesc* dd = reinterpret_cast<const CombineDesc*>(static_cast<char*>(sl->dev) + cb);
+    for (const FewLaunch& L : fl) {
+      const odmd_t h = hs[few[L.first]];
+      HIP_OK(launch_combine_few(dd + L.first, L.nd, L.nblocks, (int)h->basis, h->io == ODMD_F32, kb[few[L.first]],
+                                h->stream));
+    }
     HIP_OK(hipEventRecord(sl->done, hs[0]->stream));
     sl->used = true;
   }
   for (int32_t i = 0; i < count; ++i) {
+    if (steps[i] <= COMBINE_FEW) continue;
     const odmd_status s = launch_rollout(hs[i], steps[i], outs[i], true);
     if (s != ODMD_OK) return s;
   }

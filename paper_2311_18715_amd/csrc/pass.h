@@ -125,6 +125,16 @@ struct CombineArgs {
 };
 // out type: 0 = FP64, 1 = FP32; basis: storage type code as for launch_pass
 hipError_t launch_combine(const CombineArgs& c, int basis, int out_f32, int rb, hipStream_t s);
+// One stream of a batched read-out of a few states (device-resident table,
+// sorted by blk0); the streams of one launch share basis, out_f32 and rb.
+struct CombineDesc {
+  CombineArgs c;
+  int blk0;             // its first workgroup in the launch
+};
+constexpr int COMBINE_FEW = 4;            // states a batched read-out takes per stream, at most
+int combine_few_blocks(int64_t n, int basis);
+hipError_t launch_combine_few(const CombineDesc* d, int nd, int nblocks, int basis, int out_f32, int rb,
+                              hipStream_t s);
 
 hipError_t launch_basis_coef(DevState* st, hipStream_t s);
 // eigenvalues, and with vectors the unit eigenvectors V (cached per model)

@@ -73,3 +73,26 @@ def test_state_blocks_and_stores(basis, n, steps):
     check(m, m.predict(steps), steps)
     space = torch.empty(steps * n + 1, dtype=m.dtype, device="cuda")
     check(m, m.predict(steps, out=space[1:].view(steps, n)), steps)
+
+
+@pytest.mark.parametrize("first", [1, 4, 5])
+def test_a_few_states_of_many_streams_equal_each_streams_own(first):
+    """Read-outs of up to 4 states share a launch per storage type and live
+    bucket, longer ones do not: every stream's states equal its own call's
+    bit for bit, whatever the mix, also two rows, one workgroup's rows and one
+    more (256 threads of one FP64, two FP32 or four BF16 rows)."""
+    specs = [(n, r, b) for b in ("f64", "f32", "bf16") for n, r in ((2, 1), (256, 6), (257, 6), (1025, 20), (3001, 40))]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    models = []
+    for i, (n, r, b) in enumerate(specs):
+        g = ODMD(n, r, 1e-10, basis=b)
+        dt = torch.float64 if b == "f64" else torch.float32
+        X = torch.randn((7 + 3 * i, n), generator=gen, device="cuda", dtype=dt)
+        for k in range(len(X) - 1):
+            g.update(X[k], X[k + 1])
+        models.append(g)
+    steps = [(first + i) % 7 + 1 for i in range(len(models))]
+    one = [g.predict(k) for g, k in zip(models, steps)]
+    many = predict_batch(models, steps)
+    for a, b in zip(one, many):
+        assert a.shape == b.shape and torch.equal(a.nan_to_num(7.0), b.nan_to_num(7.0))
