@@ -411,6 +411,7 @@ odmd_status odmd_get_basis(odmd_t h, double* out);
  * allocation later) and makes every later update launch its streaming pass
  * and its small-SVD kernel with a start and an end event each, which take
  * the kernel's own begin and end timestamps; capacity 0 stops recording.
+ * For general pairs the pass is the launch that also sweeps T.
  * odmd_profile_read (synchronising) returns the summed pass and core
  * durations in milliseconds and the number of timed updates, then resets.
  */

@@ -300,17 +300,17 @@ __device__ __forceinline__ bool secular_vectors(double* A, double* V, int r, int
   // the group's lanes
   if (grp < nd) {
     const double dj = S.dj[grp];
-    double prod = 1.0;
+    double prod[2] = {1.0, 1.0};   // two short chains: fewer roundings in a row
 #pragma unroll
     for (int m = 0; m < NT; ++m) {
       const int i = gl + 8 * m, ic = min(i, nd - 1);
       const double rK = S.rK[ic], lam = (rK - dj) * (rK + dj) + S.mu[ic];   // lambda_i - d_j^2
       const double den = recip((tdj[m] - dj) * (tdj[m] + dj));
       const double f = i == grp ? lam : lam * den;
-      prod *= i < nd ? f : 1.0;
+      prod[m & 1] *= i < nd ? f : 1.0;
     }
-    prod = oct_prod(prod);
-    if (gl == 0) S.zh[grp] = S.zs[grp] * sqrt(fmax(prod, 0.0));
+    const double zz = oct_prod(prod[0]) * oct_prod(prod[1]);
+    if (gl == 0) S.zh[grp] = S.zs[grp] * sqrt(fmax(zz, 0.0));
   }
   __syncthreads();
   // Vectors of the roots: the unnormalised entries on the live rows J[jj]
@@ -321,7 +321,7 @@ __device__ __forceinline__ bool secular_vectors(double* A, double* V, int r, int
     const int i = grp;
     double ea[NT], ev[NT];
     int row[NT];
-    double sa = 0.0, sv = 0.0;
+    double pa[2] = {0.0, 0.0}, pv[2] = {0.0, 0.0}, pn[2] = {0.0, 0.0};
 #pragma unroll
     for (int m = 0; m < NT; ++m) {
       const int jc = min(gl + 8 * m, nd - 1);
@@ -335,24 +335,22 @@ __device__ __forceinline__ bool secular_vectors(double* A, double* V, int r, int
       const double a = ea[m] * recip(-((dK - dj) * (dK + dj) + mu));   // z~_j / (d_j^2 - lambda_i)
       ea[m] = in ? a : 0.0;
       ev[m] = in ? (row[m] == r ? -1.0 : dj * a) : 0.0;
-      sa = __builtin_fma(ea[m], ea[m], sa);
-      sv = __builtin_fma(ev[m], ev[m], sv);
+      pa[m & 1] = __builtin_fma(ea[m], ea[m], pa[m & 1]);
+      pv[m & 1] = __builtin_fma(ev[m], ev[m], pv[m & 1]);
     }
-    sa = oct_sum(sa);
-    sv = oct_sum(sv);
+    const double sa = oct_sum(pa[0]) + oct_sum(pa[1]), sv = oct_sum(pv[0]) + oct_sum(pv[1]);
     const double fa = sqrt(dK * dK + mu) / sqrt(sa);   // sigma' / |u|
     const double fv = 1.0 / sqrt(sv);
-    double sn = 0.0;
 #pragma unroll
     for (int m = 0; m < NT; ++m) {
       const double a = ea[m] * fa;
-      sn = __builtin_fma(a, a, sn);
+      pn[m & 1] = __builtin_fma(a, a, pn[m & 1]);
       if (gl + 8 * m < nd) {
         A[i * LDK + row[m]] = a;
         V[i * LDK + row[m]] = ev[m] * fv;
       }
     }
-    sn = oct_sum(sn);
+    const double sn = oct_sum(pn[0]) + oct_sum(pn[1]);
     if (gl == 0) sdo[i] = sqrt(sn);          // the column norm of what A holds
     for (int t = gl; t < S.ndef; t += 8) {
       A[i * LDK + S.dflist[t]] = 0.0;
@@ -1258,8 +1256,8 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   }
 
   // 6. singular values (exact column norms), descending order, truncation
-  //    (one 16-lane quarter-wave per column for the norm and for the rank;
-  //    M = r + 1 may exceed the 64 quarter-waves)
+  //    (one 16-lane quarter-wave per column for the norm, M = r + 1 may exceed
+  //    the 64 quarter-waves; eight lanes per column for its rank)
   const int qcl = tid & 15;
   if (!have_norms) {                       // uniform
     for (int col = tid >> 4; col < M; col += CORE_THREADS / 16) {
