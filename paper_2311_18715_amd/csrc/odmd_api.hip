@@ -178,16 +178,21 @@ odmd_status map_status(int bits) {
   } while (0)
 
 // Wait for the stream, then fetch and clear the latched device status.
-odmd_status sync_and_status(odmd_t h) {
-  HIP_OK(hipStreamSynchronize(h->stream));
-  int bits = 0;
-  HIP_OK(hipMemcpy(&bits, &h->st->status, sizeof(int), hipMemcpyDeviceToHost));
+// Returns and clears the latched status, given its bits after a synchronisation.
+odmd_status take_status(odmd_t h, int bits) {
   if (bits) {
     const int zero = 0;
     HIP_OK(hipMemcpy(&h->st->status, &zero, sizeof(int), hipMemcpyHostToDevice));
     __atomic_store_n(h->fb_host + 1, 0u, __ATOMIC_RELEASE);   // the host-visible copy too
   }
   return map_status(bits);
+}
+
+odmd_status sync_and_status(odmd_t h) {
+  HIP_OK(hipStreamSynchronize(h->stream));
+  int bits = 0;
+  HIP_OK(hipMemcpy(&bits, &h->st->status, sizeof(int), hipMemcpyDeviceToHost));
+  return take_status(h, bits);
 }
 
 template <typename T>
@@ -1046,19 +1051,27 @@ odmd_status odmd_eigs(odmd_t h, int32_t cap, int32_t* r, double* lam_re, double*
   if ((v_re == nullptr) != (v_im == nullptr)) return ODMD_EINVAL;
   HIP_OK(hipSetDevice(h->device));
   HIP_OK(launch_eig(h->st, v_re != nullptr, h->stream));
-  int rr = 0;
-  std::vector<double> lr(RMAX), li(RMAX), vr, vi;
+  // two copies: the counters and the status, and the eigen cache, whose
+  // arrays lie in a row (each copy to pageable memory costs the host about
+  // 10 us; field by field there were four, or six with vectors)
+  static_assert(offsetof(DevState, r) < offsetof(DevState, status) &&
+                    offsetof(DevState, lam_im) == offsetof(DevState, lam_re) + RMAX * sizeof(double) &&
+                    offsetof(DevState, V_re) == offsetof(DevState, lam_im) + RMAX * sizeof(double) &&
+                    offsetof(DevState, V_im) == offsetof(DevState, V_re) + RMAX * RMAX * sizeof(double),
+                "the copied fields lie in a row");
+  constexpr size_t head0 = offsetof(DevState, r);
+  constexpr size_t head_bytes = offsetof(DevState, status) + sizeof(int) - head0;
+  char head[head_bytes];
+  std::vector<double> cache(2 * RMAX + (v_re ? 2 * RMAX * RMAX : 0));
   odmd_status s;
-  if ((s = copy_field(h, &rr, &h->st->r, 1)) != ODMD_OK) return s;
-  if ((s = copy_field(h, lr.data(), h->st->lam_re, RMAX)) != ODMD_OK) return s;
-  if ((s = copy_field(h, li.data(), h->st->lam_im, RMAX)) != ODMD_OK) return s;
-  if (v_re) {
-    vr.resize(RMAX * RMAX);
-    vi.resize(RMAX * RMAX);
-    if ((s = copy_field(h, vr.data(), h->st->V_re, RMAX * RMAX)) != ODMD_OK) return s;
-    if ((s = copy_field(h, vi.data(), h->st->V_im, RMAX * RMAX)) != ODMD_OK) return s;
-  }
-  s = sync_and_status(h);
+  if ((s = copy_field(h, head, reinterpret_cast<const char*>(h->st) + head0, head_bytes)) != ODMD_OK) return s;
+  if ((s = copy_field(h, cache.data(), h->st->lam_re, cache.size())) != ODMD_OK) return s;
+  HIP_OK(hipStreamSynchronize(h->stream));
+  int rr = 0, bits = 0;
+  std::memcpy(&rr, head, sizeof(int));
+  std::memcpy(&bits, head + (offsetof(DevState, status) - head0), sizeof(int));
+  const double *lr = cache.data(), *li = lr + RMAX, *vr = li + RMAX, *vi = vr + RMAX * RMAX;
+  s = take_status(h, bits);
   *r = rr;
   if (s != ODMD_OK) return s;
   if (rr == 0) return ODMD_EEMPTY;
