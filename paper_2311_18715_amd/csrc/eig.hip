@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "odmd_internal.h"
 #include "pass.h"
 #include "xlane.h"
@@ -65,6 +67,13 @@ __device__ __forceinline__ double readlane_d(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Scaling by powers of two (exact), compiled in for SMALL only: the exponent
+// that brings m to [0.5, 1), zero for m = 0, and v 2^e.
+template <bool SMALL>
+__device__ __forceinline__ int exponent_of(double m) { return SMALL ? __builtin_amdgcn_frexp_exp(m) : 0; }
+template <bool SMALL>
+__device__ __forceinline__ double times_2(double v, int e) { return SMALL ? ldexp(v, e) : v; }
+
 // Householder reflector P = I - beta w w^T mapping (x, y, z) to (alpha, 0, 0),
 // w = (w0, y, z): with nrm = ||(x, y, z)|| and alpha = -sign(x) nrm,
 // w0 = x - alpha and beta = 2 / w.w = 1 / (nrm (nrm + |x|)).  Its dependent
@@ -74,12 +83,18 @@ __device__ __forceinline__ double readlane_d(double v, int lane) {
 // denominator, which runs beside the correction; the products with w run
 // beside beta.  No branch: the matrix is scaled to entries of order one, so
 // nothing overflows, and a vector whose square underflows to below 2^-900 is
-// zero for it (the identity, y and z dropped).
+// zero for it (the identity, y and z dropped).  SMALL (see eig_body): the
+// vector is brought to order one first; P is the same for any multiple of it.
 struct Reflector {
   double w0, w1, w2, beta, alpha;
 };
+template <bool SMALL>
 __device__ __forceinline__ Reflector make_reflector(double x, double y, double z) {
   constexpr double TINY = 0x1p-900;
+  const int ex = exponent_of<SMALL>(fmax(fabs(x), fmax(fabs(y), fabs(z))));
+  x = times_2<SMALL>(x, -ex);
+  y = times_2<SMALL>(y, -ex);
+  z = times_2<SMALL>(z, -ex);
   const double s0 = __builtin_fma(z, z, __builtin_fma(y, y, x * x));
   const bool ok = s0 > TINY;
   const double ss = fmax(s0, TINY);
@@ -98,7 +113,7 @@ __device__ __forceinline__ Reflector make_reflector(double x, double y, double z
   R.w1 = y;
   R.w2 = z;
   R.beta = ok ? __builtin_fma(rd, __builtin_fma(f, f, f), rd) : 0.0;
-  R.alpha = ok ? al : x;
+  R.alpha = times_2<SMALL>(ok ? al : x, ex);
   return R;
 }
 
@@ -119,78 +134,13 @@ __device__ __forceinline__ double sum8(double v) {
   return v;
 }
 
-// VECS false: eigenvalues only (no Z, eigenvectors or V); the cache level
-// eig_valid is 1 after such a call and 2 after a call with vectors.  Both
-// run the same operations on H, so the eigenvalues are the same bit for bit.
-//
-// Latency bounds it: one workgroup, a serial chain of reflectors.  The chain
-// is cut in three ways.  (1) EIG_K bulges are chased at once, EIG_GAP rows
-// apart, one wavefront each, all with the shifts of the trailing 2 x 2 block:
-// a group of K sweeps over N rows takes N - 1 + 3 (K - 1) steps instead of
-// K (N - 1), for about 1.4 times the sweeps (the K sweeps share their
-// shifts, so a group converges with order K + 1 instead of 2^K).  (2) A step
-// has two phases, a barrier after each: every bulge applies its reflector
-// to its three rows (lane t is column t), then to its three columns (lane t
-// is row t).  H is zero below the bulges and padded with zero rows and
-// columns, so no lane is masked and no entry of the 3 x 3 block is formed
-// twice.  (3) Z's columns are left to wavefronts of their own, and the
-// reduction and eigenvector sums are split over the workgroup.
-// A~ of rank 40 (n = 160,000 wake): 415 us (854 with one wavefront and one
-// bulge); with vectors at rank 64: 1137 us (2388).  A step takes about 840
-// cycles (1160 before; one bulge alone 630), with vectors 1030.
-template <bool VECS>
-__device__ __forceinline__ void eig_body(DevState* st) {
-  if (st->eig_valid >= (VECS ? 2 : 1)) return;
-  constexpr int NTH = eig_threads<VECS>();
-  __shared__ double H[(RMAX + 2) * LDH];         // zero past n x n
-  __shared__ double Z[VECS ? (RMAX + 2) * LDH : 1];
-  __shared__ double Xr[VECS ? (RMAX + 1) * LDH : 1];
-  __shared__ double Xi[VECS ? (RMAX + 1) * LDH : 1];
-  __shared__ double wr[RMAX], wi[RMAX], red[EIG_K][RMAX];
-  __shared__ double redb[NTH / 64][RMAX];
-  __shared__ Reflector rf[EIG_K][2];
-  __shared__ int pos[RMAX];
+// Steps 1 and 2: H (LDS, scaled, zero past n x n) to its real Schur form, with
+// vectors Z.  True if an eigenvalue was not found.  (SMALL: see eig_body)
+template <bool VECS, bool SMALL>
+__device__ __forceinline__ bool schur(double* H, double* Z, double* wr, double* wi, double (*red)[RMAX],
+                                      double (*redb)[RMAX], Reflector (*rf)[2], const int n, const double hn) {
   const int tid = threadIdx.x, t = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = st->r;
-  if (n == 0) {
-    if (tid == 0) {
-      st->eig_valid = 2;
-      st->eig_status = 0;
-    }
-    return;
-  }
-  // A~ scaled by a power of two to entries of order one (exact), zero past n
-  double hn = 0.0;
-  constexpr int NL = RMAX * RMAX / NTH;
-  double av[NL];                         // every load in flight at once
-#pragma unroll
-  for (int u = 0; u < NL; ++u) {
-    const int i = t, j = wave + u * (NTH / 64);
-    const bool in = i < n && j < n;
-    const double v = st->At[in ? j * RMAX + i : 0];
-    av[u] = in ? v : 0.0;
-  }
-#pragma unroll
-  for (int u = 0; u < NL; ++u) hn = fmax(hn, fabs(av[u]));
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) hn = fmax(hn, __shfl_xor(hn, o, 64));
-  if (t == 0) red[0][wave] = hn;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < NTH / 64; ++w) hn = fmax(hn, red[0][w]);
-  const int ex = hn > 0.0 && hn < INFINITY ? ilogb(hn) : 0;
-  // row RMAX and the columns past RMAX are zero too
-  for (int idx = tid; idx < 2 * LDH; idx += NTH) H[RMAX * LDH + idx] = 0.0;
-  if (tid < RMAX) H[tid * LDH + RMAX] = 0.0;
-#pragma unroll
-  for (int u = 0; u < NL; ++u) H[(wave + u * (NTH / 64)) * LDH + t] = ldexp(av[u], -ex);
-  if (VECS) {                            // Z's columns past RMAX (their values are not used)
-    for (int idx = tid; idx < 2 * LDH; idx += NTH) Z[RMAX * LDH + idx] = 0.0;
-  }
-  hn = hn > 0.0 && hn < INFINITY ? ldexp(hn, -ex) : 1.0;
-  __syncthreads();
-
   // 1. Hessenberg reduction.  Both sides of a reflector I - beta v v^T in one
   //    update from the old H, with a = beta H^T v, b = beta H v and
   //    c = b - beta (v.b) v:  H <- H - v a^T - c v^T; and Z <- Z - (beta Z v) v^T.
@@ -208,11 +158,18 @@ __device__ __forceinline__ void eig_body(DevState* st) {
   for (int e = 0; e < NE1; ++e)
     own[e] = onH ? Hm(part + EIG_K * e, t) : (t == part + EIG_K * e ? 1.0 : 0.0);
   for (int k = 0; k + 2 < n; ++k) {
-    const double hk = Hm(t, k);
+    double hk = Hm(t, k);
+    int ex = 0;
+    double top = 0.0;                    // SMALL: the largest entry to annihilate
+    if (SMALL) {
+      top = wave_max(t > k + 1 ? fabs(hk) : 0.0);
+      ex = exponent_of<SMALL>(wave_max(t > k ? fabs(hk) : 0.0));
+      hk = times_2<SMALL>(hk, -ex);
+    }
     double x2 = t > k + 1 ? hk * hk : 0.0;
     x2 = add_half_pair(add_row_pair(row_sum(x2)));
     const double x0 = readlane_d(hk, k + 1);
-    const bool none = x2 <= 0x1p-900;    // uniform: nothing to annihilate
+    const bool none = SMALL ? top == 0.0 : x2 <= 0x1p-900;    // uniform: nothing to annihilate
     const double nrm = none ? fabs(x0) : sqrt(__builtin_fma(x0, x0, x2));
     const double al = none ? x0 : (x0 >= 0.0 ? -nrm : nrm);
     const double beta = none ? 0.0 : 1.0 / (nrm * (nrm + fabs(x0)));
@@ -256,7 +213,7 @@ __device__ __forceinline__ void eig_body(DevState* st) {
       for (int e = 0; e < NE1; ++e) {
         const int i = part + EIG_K * e;
         const double g = __builtin_fma(-readlane_d(ct, i), vt, __builtin_fma(-readlane_d(vt, i), a, own[e]));
-        own[e] = colk && i > k ? (i == k + 1 ? al : 0.0) : g;
+        own[e] = colk && i > k ? (i == k + 1 ? times_2<SMALL>(al, ex) : 0.0) : g;
         Hm(i, t) = own[e];
       }
     } else {
@@ -300,10 +257,12 @@ __device__ __forceinline__ void eig_body(DevState* st) {
       const int p = hi - 1, q = hi;
       const double a = Hm(p, p), b = Hm(p, q), c = Hm(q, p), d = Hm(q, q);
       const double pp = 0.5 * (a - d);
-      const double disc = pp * pp + b * c;
+      const int ex = exponent_of<SMALL>(fmax(fabs(pp), fmax(fabs(b), fabs(c))));
+      const double ps = times_2<SMALL>(pp, -ex);
+      const double disc = ps * ps + times_2<SMALL>(b, -ex) * times_2<SMALL>(c, -ex);
       __syncthreads();
       if (disc >= 0.0) {
-        const double sq = sqrt(disc);
+        const double sq = times_2<SMALL>(sqrt(disc), ex);
         const double zz = pp + (pp >= 0.0 ? sq : -sq);
         double la = d + zz, lb = (zz != 0.0) ? d - b * c / zz : d;
         // rotation whose first column is the eigenvector (zz, c) of la
@@ -339,8 +298,8 @@ __device__ __forceinline__ void eig_body(DevState* st) {
         }
       } else if (tid == 0) {
         wr[p] = wr[q] = a - pp;          // (a + d) / 2
-        wi[p] = sqrt(-disc);
-        wi[q] = -sqrt(-disc);
+        wi[p] = times_2<SMALL>(sqrt(-disc), ex);
+        wi[q] = -times_2<SMALL>(sqrt(-disc), ex);
       }
       hi -= 2;
       its = 0;
@@ -354,15 +313,24 @@ __device__ __forceinline__ void eig_body(DevState* st) {
     ++total;
     const int N = hi - l + 1;            // at least 3
     int K = min(EIG_K, max(1, N / EIG_MIN));
-    double s, tt;
+    double s, tt;                        // the shifts' sum and product, times 2^-es and 2^-2 es
+    int es;
     if (its == 10 || its == 20) {        // exceptional shift
       const double w = fabs(Hm(hi, hi - 1)) + fabs(Hm(hi - 1, hi - 2));
-      s = 1.5 * w;
-      tt = w * w;
+      es = exponent_of<SMALL>(w);
+      const double ws = times_2<SMALL>(w, -es);
+      s = 1.5 * ws;
+      tt = ws * ws;
       K = 1;
     } else {
-      s = Hm(hi - 1, hi - 1) + Hm(hi, hi);
-      tt = Hm(hi - 1, hi - 1) * Hm(hi, hi) - Hm(hi - 1, hi) * Hm(hi, hi - 1);
+      double a = Hm(hi - 1, hi - 1), b = Hm(hi - 1, hi), c = Hm(hi, hi - 1), d = Hm(hi, hi);
+      es = exponent_of<SMALL>(fmax(fmax(fabs(a), fabs(b)), fmax(fabs(c), fabs(d))));
+      a = times_2<SMALL>(a, -es);
+      b = times_2<SMALL>(b, -es);
+      c = times_2<SMALL>(c, -es);
+      d = times_2<SMALL>(d, -es);
+      s = a + d;
+      tt = a * d - b * c;
     }
     __syncthreads();                     // the shifts (and H(l, l-1) = 0) before the first rows change
     // Bulge chase.  Bulge b starts EIG_GAP b steps after the first; its
@@ -379,16 +347,27 @@ __device__ __forceinline__ void eig_body(DevState* st) {
       idle(N - 1 + EIG_GAP * (K - 1));
     } else if (onH) {
       idle(EIG_GAP * b);
-      const double h00 = Hm(l, l), h10 = Hm(l + 1, l);
-      double x = h00 * h00 + Hm(l, l + 1) * h10 - s * h00 + tt;
-      double y = h10 * (h00 + Hm(l + 1, l + 1) - s);
-      double z = h10 * Hm(l + 2, l + 1);
+      // the first column of the shifted square (up to a power of two)
+      double h00 = Hm(l, l), h10 = Hm(l + 1, l), h01 = Hm(l, l + 1), h11 = Hm(l + 1, l + 1), h21 = Hm(l + 2, l + 1);
+      if (SMALL) {
+        const int eb = max(es, exponent_of<SMALL>(fmax(fmax(fmax(fabs(h00), fabs(h10)), fmax(fabs(h01), fabs(h11))), fabs(h21))));
+        s = times_2<SMALL>(s, es - eb);
+        tt = times_2<SMALL>(tt, 2 * (es - eb));
+        h00 = times_2<SMALL>(h00, -eb);
+        h10 = times_2<SMALL>(h10, -eb);
+        h01 = times_2<SMALL>(h01, -eb);
+        h11 = times_2<SMALL>(h11, -eb);
+        h21 = times_2<SMALL>(h21, -eb);
+      }
+      double x = h00 * h00 + h01 * h10 - s * h00 + tt;
+      double y = h10 * (h00 + h11 - s);
+      double z = h10 * h21;
       double* pc = H + t * LDH + l;                    // column t, rows k ..
       double* pr = H + l * LDH + t;                    // row t, columns k ..
       int bc = -1;                                     // bulge column: none in the first step
       for (int k = l; k < hi; ++k) {
         double c0 = pc[0], c1 = pc[1], c2 = pc[2];
-        const Reflector R = make_reflector(x, y, z);
+        const Reflector R = make_reflector<SMALL>(x, y, z);
         if (VECS && t == 0) rf[b][(k - l) & 1] = R;
         double d = -R.beta * __builtin_fma(R.w2, c2, __builtin_fma(R.w1, c1, R.w0 * c0));
         const bool bulge = t == bc;                    // it becomes (alpha, 0, 0)
@@ -434,6 +413,100 @@ __device__ __forceinline__ void eig_body(DevState* st) {
       idle(EIG_GAP * (K - 1 - b));
     }
   }
+  return fail;
+}
+
+// VECS false: eigenvalues only (no Z, eigenvectors or V); the cache level
+// eig_valid is 1 after such a call and 2 after a call with vectors.  Both
+// run the same operations on H, so the eigenvalues are the same bit for bit.
+//
+// Latency bounds it: one workgroup, a serial chain of reflectors.  The chain
+// is cut in three ways.  (1) EIG_K bulges are chased at once, EIG_GAP rows
+// apart, one wavefront each, all with the shifts of the trailing 2 x 2 block:
+// a group of K sweeps over N rows takes N - 1 + 3 (K - 1) steps instead of
+// K (N - 1), for about 1.4 times the sweeps (the K sweeps share their
+// shifts, so a group converges with order K + 1 instead of 2^K).  (2) A step
+// has two phases, a barrier after each: every bulge applies its reflector
+// to its three rows (lane t is column t), then to its three columns (lane t
+// is row t).  H is zero below the bulges and padded with zero rows and
+// columns, so no lane is masked and no entry of the 3 x 3 block is formed
+// twice.  (3) Z's columns are left to wavefronts of their own, and the
+// reduction and eigenvector sums are split over the workgroup.
+// Squares and products of two entries of a block far below the rest of the
+// matrix vanish (an exactly decoupled block of 1e-67 of the largest entry
+// never converged).  A matrix that holds such an entry, above zero and below
+// SMALL_ENTRY of the largest, takes a form of the solver that forms them from
+// entries scaled by powers of two.  The others come below that only by
+// convergence, where dropping an entry is harmless, and take the form without
+// (a test for small vectors in every step cost 46 of 1250 us, rank 64 with
+// vectors).
+// A~ of rank 40 (n = 160,000 wake): 415 us (854 with one wavefront and one
+// bulge); with vectors at rank 64: 1137 us (2388).  A step takes about 840
+// cycles (1160 before; one bulge alone 630), with vectors 1030.
+constexpr double SMALL_ENTRY = 0x1p-200;
+template <bool VECS>
+__device__ __forceinline__ void eig_body(DevState* st) {
+  if (st->eig_valid >= (VECS ? 2 : 1)) return;
+  constexpr int NTH = eig_threads<VECS>();
+  __shared__ double H[(RMAX + 2) * LDH];         // zero past n x n
+  __shared__ double Z[VECS ? (RMAX + 2) * LDH : 1];
+  __shared__ double Xr[VECS ? (RMAX + 1) * LDH : 1];
+  __shared__ double Xi[VECS ? (RMAX + 1) * LDH : 1];
+  __shared__ double wr[RMAX], wi[RMAX], red[EIG_K][RMAX];
+  __shared__ double redb[NTH / 64][RMAX];
+  __shared__ Reflector rf[EIG_K][2];
+  __shared__ int pos[RMAX], below[NTH / 64];
+  const int tid = threadIdx.x, t = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = st->r;
+  if (n == 0) {
+    if (tid == 0) {
+      st->eig_valid = 2;
+      st->eig_status = 0;
+    }
+    return;
+  }
+  // A~ scaled by a power of two to entries of order one (exact), zero past n
+  double hn = 0.0;
+  constexpr int NL = RMAX * RMAX / NTH;
+  double av[NL];                         // every load in flight at once
+#pragma unroll
+  for (int u = 0; u < NL; ++u) {
+    const int i = t, j = wave + u * (NTH / 64);
+    const bool in = i < n && j < n;
+    const double v = st->At[in ? j * RMAX + i : 0];
+    av[u] = in ? v : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < NL; ++u) hn = fmax(hn, fabs(av[u]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) hn = fmax(hn, __shfl_xor(hn, o, 64));
+  if (t == 0) red[0][wave] = hn;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NTH / 64; ++w) hn = fmax(hn, red[0][w]);
+  const int ex = hn > 0.0 && hn < INFINITY ? ilogb(hn) : 0;
+  bool low = false;
+#pragma unroll
+  for (int u = 0; u < NL; ++u) low = low || (av[u] != 0.0 && fabs(av[u]) < SMALL_ENTRY * hn);
+  const bool wave_low = __ballot(low) != 0;
+  if (t == 0) below[wave] = wave_low;
+  // row RMAX and the columns past RMAX are zero too
+  for (int idx = tid; idx < 2 * LDH; idx += NTH) H[RMAX * LDH + idx] = 0.0;
+  if (tid < RMAX) H[tid * LDH + RMAX] = 0.0;
+#pragma unroll
+  for (int u = 0; u < NL; ++u) H[(wave + u * (NTH / 64)) * LDH + t] = ldexp(av[u], -ex);
+  if (VECS) {                            // Z's columns past RMAX (their values are not used)
+    for (int idx = tid; idx < 2 * LDH; idx += NTH) Z[RMAX * LDH + idx] = 0.0;
+  }
+  hn = hn > 0.0 && hn < INFINITY ? ldexp(hn, -ex) : 1.0;
+  __syncthreads();
+  bool small_entries = false;
+#pragma unroll
+  for (int w = 0; w < NTH / 64; ++w) small_entries = small_entries || below[w] != 0;
+
+  const bool fail = small_entries ? schur<VECS, true>(H, Z, wr, wi, red, redb, rf, n, hn)
+                                  : schur<VECS, false>(H, Z, wr, wi, red, redb, rf, n, hn);
   __syncthreads();
 
   // 3. eigenvectors of the quasi-triangular T by back-substitution (complex
@@ -464,6 +537,10 @@ __device__ __forceinline__ void eig_body(DevState* st) {
         u1 = w1;
         u2 = w2;
       }
+      // (of order one, so that the squares of a small block's vector do not vanish)
+      const int eu = exponent_of<true>(fmax(fmax(fabs(u1.re), fabs(u1.im)), fmax(fabs(u2.re), fabs(u2.im))));
+      u1 = {times_2<true>(u1.re, -eu), times_2<true>(u1.im, -eu)};
+      u2 = {times_2<true>(u2.re, -eu), times_2<true>(u2.im, -eu)};
       if (el == 0) {
         xr[p] = u1.re;
         xi[p] = u1.im;
