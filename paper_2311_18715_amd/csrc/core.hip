@@ -1520,15 +1520,19 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   }
 }
 
-// One update of the small state, then the stored-column count it leaves,
+// One update of the small state, then the stored-column counts it leaves,
 // tagged with the update's sequence number, to the host-visible feedback
-// word (the host sizes later launches from it).
+// words (the host sizes later launches from them).
 template <bool GENERAL>
 __device__ __forceinline__ void core_body(const CoreArgs& c) {
   core_update<GENERAL>(c);
   if (threadIdx.x == 0 && c.fb) {
-    const unsigned mm = (unsigned)c.st->m;
-    *reinterpret_cast<volatile unsigned*>(c.fb) = ((c.seq & 0xFFFFFFu) << 8) | (mm & 0xFFu);
+    const unsigned m = (unsigned)c.st->m, mt = GENERAL ? (unsigned)c.tst->m : 0u, tag = (c.seq & 0xFFFFFFu) << 8;
+    static_assert(FB_S == 0 && FB_T == 1, "both counts in one store");
+    if (GENERAL)
+      *reinterpret_cast<volatile uint64_t*>(c.fb) = (uint64_t)(tag | (mt & 0xFFu)) << 32 | (tag | (m & 0xFFu));
+    else
+      *reinterpret_cast<volatile unsigned*>(c.fb) = tag | (m & 0xFFu);
   }
 }
 

@@ -61,7 +61,7 @@ struct odmd_s {
   std::vector<unsigned char> ev_lat;   // per timed update: recorded with prof_lat
   // Feedback: the core writes (seq << 8) | m (stored columns in use) into
   // this pinned host word after every update; seq counts the updates issued
-  // on the handle.
+  // on the handle; general pairs: the same for T's columns into the next.
   unsigned* fb_host = nullptr;
   unsigned* fb_dev = nullptr;
   // BF16 basis: records of the Gram kernel that follows each pass (the Gram
@@ -183,7 +183,7 @@ odmd_status take_status(odmd_t h, int bits) {
   if (bits) {
     const int zero = 0;
     HIP_OK(hipMemcpy(&h->st->status, &zero, sizeof(int), hipMemcpyHostToDevice));
-    __atomic_store_n(h->fb_host + 1, 0u, __ATOMIC_RELEASE);   // the host-visible copy too
+    __atomic_store_n(h->fb_host + FB_STATUS, 0u, __ATOMIC_RELEASE);   // the host-visible copy too
   }
   return map_status(bits);
 }
@@ -207,13 +207,13 @@ odmd_status copy_field(odmd_t h, T* dst, const T* src_dev, size_t count) {
 int fold_slack(odmd_t h) { return h->basis == ODMD_BF16 ? 0 : FOLD_SLACK; }
 
 // Live-column bucket for the next pass: an upper bound on the stored
-// columns in use after the last issued update.  They grow by at most one per
-// update, so the last count the device reported plus the number of updates
-// issued since bounds them.  The bucket is a multiple of 8 and never exceeds
-// the tile capacity.
-int live_bucket(odmd_t h) {
+// columns in use after the last issued update (of S; of T with FB_T).  They
+// grow by at most one per update, so the last count the device reported plus
+// the number of updates issued since bounds them.  The bucket is a multiple of
+// 8 and never exceeds the tile capacity.
+int live_bucket(odmd_t h, int word = FB_S) {
   if (h->full_bucket) return h->ct;
-  const unsigned v = __atomic_load_n(h->fb_host, __ATOMIC_ACQUIRE);
+  const unsigned v = __atomic_load_n(h->fb_host + word, __ATOMIC_ACQUIRE);
   const unsigned lag = (h->seq - (v >> 8)) & 0xFFFFFFu;
   const int64_t bound = std::min<int64_t>(h->ct, (int64_t)(v & 0xFFu) + lag);
   return std::max(8, col_bucket((int)bound));
@@ -290,9 +290,14 @@ odmd_status launch_update(odmd_t h, const void* x, const void* y) {
   p.threads = h->threads;
   p.rows2 = h->rows2;
   const int kb = live_bucket(h);
-  // (T's column count is not in the host's feedback: its sweep, and the pass
-  // beside it, take the capacity's bucket)
-  const int pass_kb = h->general ? h->ct : kb;
+  // One bucket for both sweeps of a general pair, so the larger count's: T
+  // gains a column with every pair and S only with a new direction, but both
+  // are rewritten at the rank plus FOLD_SLACK, so that S reads at most two
+  // buckets too many (from cache).  FP64, n = 1M, r_max = 64, an update of a
+  // model of 10 directions: 181 us with a launch for each sweep, 184 with one
+  // at the capacity's bucket, 173 at the larger count's; of 32 directions 276,
+  // 264 and 261.
+  const int pass_kb = h->general ? std::max(kb, live_bucket(h, FB_T)) : kb;
   if (h->general) {
     // U^T x from a projection sweep, then the coefficients of the streaming
     // pass (which also writes e contiguously for the T sweep below)
@@ -339,7 +344,7 @@ odmd_status launch_update(odmd_t h, const void* x, const void* y) {
   c.seq = h->seq;
   c.tst = h->general ? h->tst : nullptr;
   c.pt = h->general ? h->pt : nullptr;
-  c.rbt = h->ct;
+  c.rbt = pass_kb;
   HIP_OK(launch_core(c, h->stream, ev && !lat ? ev[2] : nullptr, ev ? ev[3] : nullptr));
   return ODMD_OK;
 }
@@ -704,7 +709,7 @@ odmd_status launch_rollout(odmd_t h, int32_t steps, void* out, bool first_done =
 
 // ---- pinned feedback words: a per-device pool ----
 // Each handle holds one 64-byte slot of mapped, coherent pinned host memory
-// (the rank feedback and the status mirror).  Allocating and freeing pinned
+// (the feedback of the stored columns and the status mirror).  Allocating and freeing pinned
 // memory synchronises the device, so slots come from chunks that live until
 // the process ends.  A slot given back while the handle's work may still
 // write it waits behind an event recorded on the handle's stream.
@@ -909,7 +914,7 @@ static odmd_status create_impl(int64_t n, int32_t r_max, double tol, odmd_dtype 
     delete s;
     return ODMD_EDEVICE;
   }
-  // word 0: the rank feedback, word 1: host-visible copy of the latched status
+  // feedback of the stored columns, and the host-visible copy of the latched status
   if (!fb_acquire(s->device, &s->fb_host, &s->fb_dev)) {
     delete s;
     return ODMD_ENOMEM;
@@ -951,7 +956,7 @@ static odmd_status create_impl(int64_t n, int32_t r_max, double tol, odmd_dtype 
     delete s;
     return ODMD_EDEVICE;
   }
-  hipLaunchKernelGGL(k_init_state, dim3(1), dim3(64), 0, s->stream, s->st, s->tol_eff, s->fb_dev + 1,
+  hipLaunchKernelGGL(k_init_state, dim3(1), dim3(64), 0, s->stream, s->st, s->tol_eff, s->fb_dev + FB_STATUS,
                      general ? 1 : 0);
   if (hipGetLastError() != hipSuccess) {
     (void)hipStreamSynchronize(s->stream);
@@ -1035,7 +1040,7 @@ odmd_status odmd_update_batch_noalloc(odmd_t* hs, const void* const* xs, const v
 
 odmd_status odmd_peek_status(odmd_t h, odmd_status* status) {
   if (!h || !status) return ODMD_EINVAL;
-  *status = map_status((int)__atomic_load_n(h->fb_host + 1, __ATOMIC_ACQUIRE));
+  *status = map_status((int)__atomic_load_n(h->fb_host + FB_STATUS, __ATOMIC_ACQUIRE));
   return ODMD_OK;
 }
 

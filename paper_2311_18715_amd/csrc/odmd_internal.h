@@ -72,6 +72,11 @@ constexpr int P_YY = 2 * CMAX + 3;   // y . y
 constexpr int P_XH = 2 * CMAX + 4;   // h . x  (row-hashed weights, see row_weight)
 constexpr int P_YH = 2 * CMAX + 5;   // h . y
 
+// words of a handle's host-visible memory: stored columns in use (with the
+// update's sequence number; T's for general pairs), and the mirror of the
+// latched status
+constexpr int FB_S = 0, FB_T = 1, FB_STATUS = 2;
+
 // latched status bits
 constexpr int ST_NONFINITE = 1;
 constexpr int ST_SEQ = 2;

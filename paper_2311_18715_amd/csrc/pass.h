@@ -91,7 +91,8 @@ struct CoreArgs {
   int ct;               // stored-column capacity of the stream
   int fold_slack;       // refold once the stored columns reach r' + fold_slack
                         // (or the capacity); 0: only at the capacity
-  unsigned* fb;         // host-visible word: (seq << 8) | stored columns after this update
+  unsigned* fb;         // host-visible words: (seq << 8) | stored columns after this update, at
+                        // FB_S for S and at FB_T for T (general pairs)
   unsigned seq;         // update sequence number (24 bits) of this launch
   DevState* tst;        // general pairs: state of B = T R (R in its Q), else null
   const double* pt;     // general pairs: T sweep records, T^T e in the second half

@@ -172,3 +172,46 @@ def test_general_edge_cases():
     with pytest.raises(OdmdError) as e:
         update_batch([h], [Xd[0]], [Xd[1]])
     assert e.value.name == "EINVAL"
+
+
+@pytest.mark.parametrize("basis,n,shape", [("f64", 5003, None), ("f64", 131072, None), ("f32", 5003, (512, 64, 1024)), ("bf16", 5003, None)])
+@pytest.mark.parametrize("rank", [0, 3, 9, 30])
+def test_bucket_of_both_sweeps_changes_no_bit(basis, n, shape, rank):
+    """A model far below its cap runs both sweeps at the bucket of the larger
+    of the two stored-column counts; a handle whose update was captured once
+    runs them at the capacity's.  Noise-free pairs (T gains a column with
+    every pair, S none once the rank is reached), pairs with noise (both
+    refold), a skipped pair and one whose x is zero: every state equal, with
+    the host up to 40 updates ahead of the device or none."""
+    dt = torch.float64 if basis == "f64" else torch.float32
+    S = torch.cuda.Stream()
+    a = ODMD(n, 64, 1e-8, basis=basis, pairs="general", shape=shape, stream=S)
+    b = ODMD(n, 64, 1e-8, basis=basis, pairs="general", shape=shape, stream=S)
+    gen = torch.Generator(device="cuda").manual_seed(n + rank)
+    modes = torch.randn((max(rank, 1), n), generator=gen, device="cuda", dtype=torch.float64)
+    coef = torch.randn((100, 2, max(rank, 1)), generator=gen, device="cuda", dtype=torch.float64) * (rank > 0)
+    P = (coef.reshape(200, -1) @ modes).reshape(100, 2, n)
+    P[60:] += 1e-3 * torch.randn((40, 2, n), generator=gen, device="cuda", dtype=torch.float64)
+    P[30, 0, 7] = float("nan")
+    P[45, 0] = 0.0
+    P = P.to(dt)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=S):
+        b.update(P[0, 0], P[0, 1])                # not replayed
+    for k in range(100):
+        a.update(P[k, 0], P[k, 1])
+        b.update(P[k, 0], P[k, 1])
+        if k in (10, 11, 12, 31, 55, 56, 70, 99):
+            for m in (a, b):
+                if k == 31:
+                    with pytest.raises(OdmdError) as e:
+                        m.sync()
+                    assert e.value.name == "ENONFINITE"
+                else:
+                    m.sync()
+            sa, sb = a.state(), b.state()
+            assert a.info().stored == b.info().stored and sa["r"] == sb["r"]
+            for key in ("sigma", "atilde", "p_y", "C", "w"):
+                assert np.array_equal(sa[key], sb[key]), (k, key)
+    assert torch.equal(a.basis_matrix(), b.basis_matrix())
