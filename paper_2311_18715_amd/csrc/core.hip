@@ -417,9 +417,7 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
       else S.dflist[nd0 + (j1 - 64 - p1)] = j1;
     }
     int nl = nl0 + __popcll(m1), ndef = n - nl;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
     // tied poles (rare): detected in parallel, merged serially by lane 0
     bool tie = false;
     for (int k = tid; k + 1 < nl; k += 64) {
@@ -450,9 +448,7 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
       nl = __shfl(nl, 0, 64);
       ndef = __shfl(ndef, 0, 64);
       ngiv = __shfl(ngiv, 0, 64);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      wave_lds_fence();
       for (int t = tid; t < nl; t += 64) stage(t, S.J[t], S.d[S.J[t]], S.z[S.J[t]]);
     }
     if (tid == 0) {

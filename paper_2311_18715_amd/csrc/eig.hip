@@ -50,15 +50,6 @@ __device__ __forceinline__ double cabs2(cplx a) { return hypot(a.re, a.im); }
 #define Hm(i, j) H[(j) * LDH + (i)]
 #define Zm(i, j) Z[(j) * LDH + (i)]
 
-// LDS written by some lanes of a wavefront is read by others of it next (the
-// wavefront's LDS operations complete in order; the fence keeps the compiler
-// from reordering them)
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The value of v in the given lane (a wave-uniform index), in every lane.
 __device__ __forceinline__ double readlane_d(double v, int lane) {
   const long long b = __double_as_longlong(v);

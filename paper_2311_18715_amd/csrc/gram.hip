@@ -25,6 +25,7 @@
 
 #include "odmd_internal.h"
 #include "pass.h"
+#include "xlane.h"
 
 namespace odmd {
 
@@ -79,6 +80,7 @@ __device__ __forceinline__ void gram_body(const GramArgs& g, int wg) {
 #pragma unroll
     for (int i = 0; i < NL; ++i)
       *reinterpret_cast<h8_t*>(sw + (8 * i + (lane >> 3)) * GRAM_LD + 8 * (lane & 7)) = next[i];
+    wave_lds_fence();                        // other lanes read them
     load_tile(t + NW < t1 ? t + NW : t, next);   // under this tile's products
 #pragma unroll
     for (int j = 0; j < 4; ++j) {            // sixteen rows at a time
@@ -99,6 +101,7 @@ __device__ __forceinline__ void gram_body(const GramArgs& g, int wg) {
           }
         }
     }
+    wave_lds_fence();                        // the next tile takes their place
   }
   // waves in index order into one LDS record, then the record to memory:
   // entry p * 256 + 4 lane + v is the (4 (lane/16) + v, lane%16) element of

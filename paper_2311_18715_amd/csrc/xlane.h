@@ -7,6 +7,15 @@
 
 namespace odmd {
 
+// LDS written by some lanes of a wavefront is read by others of it next (the
+// wavefront's LDS operations complete in order; the fence keeps the compiler
+// from reordering them)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
