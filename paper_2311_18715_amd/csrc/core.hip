@@ -766,6 +766,12 @@ __device__ __forceinline__ void general_tail(const CoreArgs& c, int r, int rn, i
 // Y <- Y T, Z <- T Z, T = (3 I - Z Y) / 2 from Y = M, Z = I, quadratically
 // convergent for ||I - M|| < 1 (Higham, Functions of Matrices, 2008, 6.3);
 // its products are 16x16 FP64 matrix-core tiles, one per wave.
+// General pairs: G = U^T B stays as it is.  With D = S' - U the new basis
+// differs from U inside span(U) by U (U^T D - D^T U) / 2, the antisymmetric
+// half only, so that G is off by that half and M^-1/2 G by all of D^T U G.  In
+// a CPU model of the storage's arithmetic (restarted wake pairs, eight refolds)
+// G left alone ended 5.0e-4 from U^T B at n = 4514 and 1.7e-4 at n = 30,000,
+// carried along as M^-1/2 G 6.3e-4 and 2.4e-4.
 __device__ void gram_fix(const CoreArgs& c, int r, double* sA, double* sV, double* sQ, double* pvec,
                          double* p2, double* pyr) {
   const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;

@@ -215,3 +215,47 @@ def test_bucket_of_both_sweeps_changes_no_bit(basis, n, shape, rank):
             for key in ("sigma", "atilde", "p_y", "C", "w"):
                 assert np.array_equal(sa[key], sb[key]), (k, key)
     assert torch.equal(a.basis_matrix(), b.basis_matrix())
+
+
+@pytest.mark.parametrize("basis,n,r,shape", [
+    ("bf16", 4515, 14, None),                   # 256 threads, one row a lane
+    ("bf16", 1001, 14, (512, 64, 1024)),        # 512 threads, two rows a lane: 32-row units, the last one ragged
+    ("bf16", 1000, 6, (512, 16, 1024)),         # 63 workgroups for 32 units: some have none
+    ("bf16", 131105, 30, None),                 # the wide default shape
+    ("f32", 1482927, 6, None),                  # the first sizes with two FP32 rows a lane
+    ("f32", 1482927, 14, (512, 16, 65536)),     # more workgroups than units
+])
+def test_reduced_storage_in_every_form_of_both_sweeps(basis, n, r, shape):
+    """BF16 and FP32 columns through the pass and the T sweep that reads back
+    its residual, against the FP64 oracle on the same FP32 pairs.
+
+    Unrelated Gaussian x of r directions, y by an orthogonal operator, the
+    rank cap at r: the singular values are alike, so an error in a basis
+    column reaches the results at its own size.  A stored value is off by at
+    most eps of itself (2^-9 for BF16, 2^-24 for FP32) and the columns are
+    rounded again at each refold, so sigma and the predicted state are within
+    eps (refolds + 1) in norm (a model of the storage's arithmetic on the CPU
+    has a quarter of that, the errors being random)."""
+    pairs, eps, tol = 90 if n < 1000000 else 50, {"bf16": 2.0 ** -9, "f32": 2.0 ** -24}[basis], 2.0 ** -12 if basis == "bf16" else 1e-8
+    gen = torch.Generator(device="cuda").manual_seed(n + r)
+    draw = lambda *s: torch.randn(s, generator=gen, device="cuda", dtype=torch.float64)
+    modes, coef, A = draw(r, n), draw(pairs, r), torch.linalg.qr(draw(r, r))[0]
+    X, Y = (coef @ modes).float(), (coef @ A @ modes).float()
+    g = ODMD(n, r, tol, basis=basis, pairs="general", shape=shape)
+    o = O.OnlineDMDF1(n, r, tol)
+    stored = [0]
+    for x, y in zip(X, Y):
+        g.update(x, y)
+        o.update(x.double().cpu().numpy(), y.double().cpu().numpy())
+        stored.append(g.info().stored)
+    refolds = sum(b < a for a, b in zip(stored, stored[1:]))
+    assert refolds >= 2 and g.info().capacity < pairs       # T gains a column with every pair: it refolds too
+    bound = eps * (refolds + 1)
+    s = g.state()
+    assert s["r"] == o.r == r
+    np.testing.assert_allclose(s["sigma"], o.sigma, rtol=bound)
+    U = g.basis_matrix().double()
+    assert torch.linalg.norm(U.T @ U - torch.eye(r, dtype=U.dtype, device=U.device)).item() < bound
+    ref = o.predict(1).reshape(-1)
+    got = g.predict(1).double().cpu().numpy().reshape(-1)
+    assert np.linalg.norm(got - ref) <= bound * np.linalg.norm(ref)
