@@ -26,7 +26,7 @@ struct PassArgs {
 // basis: storage type (0 double, 1 float, 2 bf16; the odmd_dtype codes);
 // rb: live-column bucket of the launch (multiple of 8, >= the stored
 // columns in use m, <= the tile capacity ct).  e0 / e1 (may be null): events
-// that take the kernel's own start and end timestamps.
+// that take the kernel's own start and end timestamps.  p.eout must be null.
 hipError_t launch_pass(const PassArgs& p, int basis, int rb, hipStream_t s,
                        hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // General pairs: the pass p (p.eout set) and the T sweep t that reads its e,

@@ -150,6 +150,7 @@ static hipError_t launch_any(const PassArgs& p, const PassArgs* t, int basis, in
 
 hipError_t launch_pass(const PassArgs& p, int basis, int rb, hipStream_t s, hipEvent_t e0,
                        hipEvent_t e1) {
+  if (p.eout) return hipErrorInvalidValue;   // written by launch_pass_pair's kernel only
   return launch_any(p, nullptr, basis, rb, false, s, e0, e1);
 }
 
