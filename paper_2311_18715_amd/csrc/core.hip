@@ -150,11 +150,10 @@ static_assert(MMAX <= CORE_THREADS / 8, "one group of eight lanes per root");
 struct SecShared {
   double dj[MMAX], zz[MMAX], zs[MMAX];   // live poles (descending), z^2, sign of z
   double rK[MMAX], mu[MMAX];             // root i: lambda_i = rK[i]^2 + mu[i]
-  double zh[MMAX], nrm[2 * MMAX];
+  double zh[MMAX];
   double gc[MMAX], gs[MMAX], d[MMAX], z[MMAX];
   int J[MMAX], gi[MMAX], gj[MMAX], dflist[MMAX];
   int nd, ndef, ngiv, fail;
-  double tol;
 };
 
 // 1/x from the hardware reciprocal estimate and two Newton steps
@@ -452,7 +451,6 @@ __device__ __forceinline__ bool secular_svd(double* A, double* V, const double* 
       for (int t = tid; t < nl; t += 64) stage(t, S.J[t], S.d[S.J[t]], S.z[S.J[t]]);
     }
     if (tid == 0) {
-      S.tol = tl;
       S.fail = 0;
       S.nd = nl;
       S.ndef = ndef;

@@ -117,14 +117,6 @@ constexpr int EIG_MIN = 5;               // active rows per bulge, at least
 template <bool VECS>
 constexpr int eig_threads() { return (VECS ? 2 : 1) * EIG_K * 64; }
 
-// sum over groups of eight neighbouring lanes (every lane gets it)
-__device__ __forceinline__ double sum8(double v) {
-  v += dpp_move<0xB1>(v);    // quad_perm [1, 0, 3, 2]
-  v += dpp_move<0x4E>(v);    // quad_perm [2, 3, 0, 1]
-  v += dpp_move<0x141>(v);   // row_half_mirror
-  return v;
-}
-
 // Steps 1 and 2: H (LDS, scaled, zero past n x n) to its real Schur form, with
 // vectors Z.  True if an eigenvalue was not found.  (SMALL: see eig_body)
 template <bool VECS, bool SMALL>
@@ -558,10 +550,10 @@ __device__ __forceinline__ void eig_body(DevState* st) {
         ur = __builtin_fma(g, vr, ur);
         ui = __builtin_fma(g, vi, ui);
       }
-      sr = sum8(sr);
-      si = sum8(si);
-      ur = sum8(ur);
-      ui = sum8(ui);
+      sr = oct_sum(sr);
+      si = oct_sum(si);
+      ur = oct_sum(ur);
+      ui = oct_sum(ui);
       if (!blk) {
         cplx den = csub({Hm(i, i), 0.0}, lam);
         if (cabs2(den) < smin) den = {smin, 0.0};
@@ -653,7 +645,7 @@ __device__ __forceinline__ void eig_body(DevState* st) {
           }
         }
       }
-      nrm2 = sum8(nrm2);
+      nrm2 = oct_sum(nrm2);
 #pragma unroll
       for (int o = 4; o > 0; o >>= 1) {
         const double ob = __shfl_xor(best, o, 8), orr = __shfl_xor(vbr, o, 8), oi = __shfl_xor(vbi, o, 8);

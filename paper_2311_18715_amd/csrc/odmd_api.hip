@@ -177,7 +177,6 @@ odmd_status map_status(int bits) {
     }                                       \
   } while (0)
 
-// Wait for the stream, then fetch and clear the latched device status.
 // Returns and clears the latched status, given its bits after a synchronisation.
 odmd_status take_status(odmd_t h, int bits) {
   if (bits) {
@@ -188,6 +187,7 @@ odmd_status take_status(odmd_t h, int bits) {
   return map_status(bits);
 }
 
+// Wait for the stream, then fetch and clear the latched device status.
 odmd_status sync_and_status(odmd_t h) {
   HIP_OK(hipStreamSynchronize(h->stream));
   int bits = 0;

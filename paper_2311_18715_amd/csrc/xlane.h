@@ -56,14 +56,6 @@ __device__ __forceinline__ double oct_prod(double v) {
   return v;
 }
 
-__device__ __forceinline__ double row_prod(double v) {
-  v *= dpp_move<0xB1>(v);
-  v *= dpp_move<0x4E>(v);
-  v *= dpp_move<0x141>(v);
-  v *= dpp_move<0x140>(v);
-  return v;
-}
-
 // v + the value of the same lane position in the neighbouring 16-lane row
 // (rows 0 <-> 1, 2 <-> 3): the swap leaves own and partner value in its two
 // outputs
