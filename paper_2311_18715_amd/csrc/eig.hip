@@ -118,12 +118,13 @@ template <bool VECS>
 constexpr int eig_threads() { return (VECS ? 2 : 1) * EIG_K * 64; }
 
 // Steps 1 and 2: H (LDS, scaled, zero past n x n) to its real Schur form, with
-// vectors Z.  True if an eigenvalue was not found.  (SMALL: see eig_body)
+// vectors Z.  True if an eigenvalue was not found.  (SMALL: see eig_body.  The
+// thread's indexes are handed in: formed again here, the same code took 1 %
+// longer at rank 64 with vectors.)
 template <bool VECS, bool SMALL>
 __device__ __forceinline__ bool schur(double* H, double* Z, double* wr, double* wi, double (*red)[RMAX],
-                                      double (*redb)[RMAX], Reflector (*rf)[2], const int n, const double hn) {
-  const int tid = threadIdx.x, t = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+                                      double (*redb)[RMAX], Reflector (*rf)[2], const int n, const double hn,
+                                      const int tid, const int t, const int wave) {
   // 1. Hessenberg reduction.  Both sides of a reflector I - beta v v^T in one
   //    update from the old H, with a = beta H^T v, b = beta H v and
   //    c = b - beta (v.b) v:  H <- H - v a^T - c v^T; and Z <- Z - (beta Z v) v^T.
@@ -488,8 +489,8 @@ __device__ __forceinline__ void eig_body(DevState* st) {
 #pragma unroll
   for (int w = 0; w < NTH / 64; ++w) small_entries = small_entries || below[w] != 0;
 
-  const bool fail = small_entries ? schur<VECS, true>(H, Z, wr, wi, red, redb, rf, n, hn)
-                                  : schur<VECS, false>(H, Z, wr, wi, red, redb, rf, n, hn);
+  const bool fail = small_entries ? schur<VECS, true>(H, Z, wr, wi, red, redb, rf, n, hn, tid, t, wave)
+                                  : schur<VECS, false>(H, Z, wr, wi, red, redb, rf, n, hn, tid, t, wave);
   __syncthreads();
 
   // 3. eigenvectors of the quasi-triangular T by back-substitution (complex
@@ -520,10 +521,12 @@ __device__ __forceinline__ void eig_body(DevState* st) {
         u1 = w1;
         u2 = w2;
       }
-      // (of order one, so that the squares of a small block's vector do not vanish)
-      const int eu = exponent_of<true>(fmax(fmax(fabs(u1.re), fabs(u1.im)), fmax(fabs(u2.re), fabs(u2.im))));
-      u1 = {times_2<true>(u1.re, -eu), times_2<true>(u1.im, -eu)};
-      u2 = {times_2<true>(u2.re, -eu), times_2<true>(u2.im, -eu)};
+      if (small_entries) {
+        // (of order one, so that the squares of a small block's vector do not vanish)
+        const int eu = exponent_of<true>(fmax(fmax(fabs(u1.re), fabs(u1.im)), fmax(fabs(u2.re), fabs(u2.im))));
+        u1 = {times_2<true>(u1.re, -eu), times_2<true>(u1.im, -eu)};
+        u2 = {times_2<true>(u2.re, -eu), times_2<true>(u2.im, -eu)};
+      }
       if (el == 0) {
         xr[p] = u1.re;
         xi[p] = u1.im;
