@@ -75,3 +75,18 @@ def test_bf16_refold_gram_edges(n, r_max):
     assert U.shape[1] == r_max
     orth = torch.linalg.norm(U.T @ U - torch.eye(r_max, dtype=U.dtype, device=U.device), 2).item()
     assert orth < (5e-3 if n < 8000 else 2e-3)
+
+
+@pytest.mark.parametrize("pairs", ["chained", "general"])
+@pytest.mark.parametrize("r_max", [1, 7, 15, 16, 23, 24, 25, 47, 48, 49, 63, 64])
+def test_no_update_falls_back_to_jacobi(r_max, pairs):
+    """The Jacobi fallback gives the same singular values, so a root that the
+    secular solver missed shows only in the count of its sweeps: it is zero
+    after every update, while the rank grows and at the cap."""
+    rng = np.random.default_rng(300 + r_max)
+    X = torch.from_numpy(rng.standard_normal((r_max + 15, 900))).cuda()
+    Y = torch.from_numpy(rng.standard_normal((r_max + 15, 900))).cuda() if pairs == "general" else X[1:]
+    g = ODMD(900, r_max, 1e-10, pairs=pairs)
+    for j in range(r_max + 14):
+        g.update(X[j], Y[j])
+        assert g.info().last_sweeps == 0, j

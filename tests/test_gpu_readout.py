@@ -96,3 +96,48 @@ def test_a_few_states_of_many_streams_equal_each_streams_own(first):
     many = predict_batch(models, steps)
     for a, b in zip(one, many):
         assert a.shape == b.shape and torch.equal(a.nan_to_num(7.0), b.nan_to_num(7.0))
+
+
+@pytest.mark.parametrize("n,r", [(1, 1), (2, 2), (3, 3), (63, 4), (64, 4), (65, 3), (257, 2), (511, 4), (1025, 1), (4099, 4)])
+@pytest.mark.parametrize("steps", [1, 4])
+def test_few_states_equal_the_first_of_many(n, r, steps):
+    """With a rank cap of at most four odmd_get_basis runs the few-state
+    kernel too, so the reference here is the other one: the first states of a
+    rollout of 17 (FP64 matrix cores: the same sums in another order)."""
+    m = model(n, r, "f64", 12)
+    got, ref = m.predict(steps), m.predict(17)[:steps]
+    assert torch.isfinite(ref).all() and ref.abs().max() > 0
+    assert (got - ref).abs().max() <= 1e-12 * ref.abs().max()
+
+
+@pytest.mark.parametrize("basis", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("n", [1, 2, 3, 4])
+@pytest.mark.parametrize("steps", [1, 4])
+def test_few_states_of_a_few_rows(basis, n, steps):
+    """Fewer rows than the matrix-core kernels' basis reference needs: with as
+    many directions as rows nothing is truncated, and the states are A^k y
+    with A = Y X^+ of all pairs.  A stored column is off by at most eps of
+    itself and none is rewritten in 12 updates; that moves A by at most
+    2 kappa sqrt(n) eps of it (kappa the condition of X), so k steps by twice k
+    times that."""
+    m = model(n, n, basis, 12)
+    X = m._keep.double().cpu().numpy().T
+    A = X[:, 1:] @ np.linalg.pinv(X[:, :-1])
+    eps = {"f64": 1e-13, "f32": 2.0 ** -24, "bf16": 2.0 ** -9}[basis]
+    got = m.predict(steps).double().cpu().numpy()
+    state, kappa, size = X[:, -1], np.linalg.cond(X[:, :-1]), np.linalg.norm(A, 2)
+    assert m.info().r == n and m.info().stored < m.info().capacity
+    for k in range(1, steps + 1):
+        state = A @ state
+        assert np.linalg.norm(got[k - 1] - state) <= 4 * k * kappa * np.sqrt(n) * eps * size ** k * np.linalg.norm(X[:, -1])
+
+
+def test_batched_few_states_are_finite():
+    """Streams of a live rank have finite states, in a batch as by themselves
+    (equal bits of two non-finite results would say nothing)."""
+    models = [model(n, r, b, 12) for b in ("f64", "f32", "bf16") for n, r in ((2, 1), (256, 6), (1025, 9), (3001, 11))]
+    assert all(m.info().r > 0 for m in models)
+    for steps in (1, 4):
+        for m, states in zip(models, predict_batch(models, [steps] * len(models))):
+            assert torch.isfinite(states).all() and states.abs().max() > 0
+            assert torch.equal(states, m.predict(steps))
