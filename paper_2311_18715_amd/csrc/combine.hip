@@ -19,7 +19,7 @@
 // a contiguous share of the rows and 16 NS states; the stored columns are
 // read once per 16 NS states.  FP32 states from FP32 or BF16 stored columns
 // take the FP32 matrix cores instead (128-byte stores); a few states
-// (K <= 4) take one row or a few per lane.
+// (K <= 4) take one row per lane.
 //
 // The writes bound it, and how they are made decides their rate.  A state's
 // rows start at any multiple of the element size, so a wavefront's piece of
@@ -232,54 +232,42 @@ __device__ __forceinline__ void combine32_body(const CombineArgs& c, const int b
 }
 
 // A few states (a one-step prediction, Sec. 2.3's u(t + dt)): bound by the
-// read of the stored columns, not by the flops.  A lane reads 8 bytes of a
-// column (one FP64, two FP32 or four BF16 rows), so a wave reads 512 bytes
-// of every column, and the coefficients of each state are uniform across
-// the wave (scalar loads); the stored values are read once for all the
-// states of the launch.  For FP32 and BF16
-// storage every column's load is issued before the first value is used, and
-// without a test (a column past the m live ones re-reads column 0, a cache
-// hit, against a zero coefficient; stored values are finite): with the load
-// and its conversion under a test per column, each column waited for the
-// one before.  One state at n = 6M with 72 columns: FP32 997 -> 294 us
-// (5.9 TB/s), BF16 782 -> 134 us (6.4 TB/s); FP64, which needs no
-// conversion and keeps the test (it skips the loads of a short bucket), 595 us
-// (5.8 TB/s).
+// read of the stored columns, not by the flops.  One row per lane (a wave
+// reads 64 consecutive rows of a column, one 64-row tile), the coefficients of
+// each state uniform across the wave (scalar loads); the stored values are
+// read once for all the states of the launch.  For FP32 and BF16 storage every
+// column's load is issued before the first value is used, and without a test
+// (a column past the m live ones re-reads column 0, a cache hit, against a
+// zero coefficient; stored values are finite): with the load and its
+// conversion under a test per column, each column waited for the one before.
+// FP64, which needs no conversion, keeps the test (it skips the loads of a
+// short bucket).  One state at n = 6M with 72 columns: FP32 929 -> 277 us, BF16
+// 911 -> 143 us, FP64 558 us (6.2 TB/s).  Lanes of 8 bytes (two FP32, four BF16
+// rows) were no faster for one state (279 and 156 us) and slower for more,
+// each conversion made again for each state: four states of a BF16 basis of
+// 72 columns, n = 6M 268 against 185 us, n = 20,000 33 against 19 us.
 template <typename TS, typename TO, int RB>
 __device__ __forceinline__ void combine_rows_body(const CombineArgs& c, const int64_t blk) {
   typedef Storage<TS> SC;
-  constexpr int RPL = 8 / (int)sizeof(TS);   // rows per lane
+  typedef typename std::conditional<sizeof(TS) == 8, uint64_t, uint32_t>::type raw_t;
   const int m = c.st->m;
-  const int64_t row0 = (blk * 256 + threadIdx.x) * RPL;   // 64 / RPL lanes per tile
-  if (row0 >= c.n) return;
-  // (rows of the last tile past n exist and are zero)
-  const gbytes T = (gbytes)(static_cast<const TS*>(c.Us) + (row0 >> 6) * (int64_t)c.ct * 64 + (row0 & 63));
-  uint64_t u[RB];
+  const int64_t row = blk * CB_THREADS + threadIdx.x;
+  if (row >= c.n) return;
+  const gbytes T = (gbytes)(static_cast<const TS*>(c.Us) + (row >> 6) * (int64_t)c.ct * 64 + (row & 63));
+  raw_t u[RB];
 #pragma unroll
   for (int j = 0; j < RB; ++j) {
-    if constexpr (RPL > 1) u[j] = gload8(T + (j < m ? j : 0) * 64 * (int)sizeof(TS));
-    else u[j] = j < m ? gload8(T + j * 64 * (int)sizeof(TS)) : 0;
+    if constexpr (sizeof(TS) == 8) u[j] = j < m ? SC::row(T + j * 64 * (int)sizeof(TS)) : 0;
+    else u[j] = (raw_t)SC::row(T + (j < m ? j : 0) * 64 * (int)sizeof(TS));
   }
   typedef const __attribute__((address_space(4))) double* cdp;
   cdp A = (cdp)c.st->coefA;
   TO* __restrict__ out = static_cast<TO*>(c.out);
   for (int k = 0; k < c.K; ++k) {
-    double acc[RPL];
+    double acc = 0.0;
 #pragma unroll
-    for (int e = 0; e < RPL; ++e) acc[e] = 0.0;
-#pragma unroll
-    for (int j = 0; j < RB; ++j) {
-      const double a = A[k * CMAX + j];
-      // (an empty asm statement that claims to change the packed rows: the
-      // conversions stay here, not hoisted out of the loop over the states,
-      // where they would hold every row of every column in FP64)
-      if constexpr (RPL > 1) asm volatile("" : "+v"(u[j]));
-#pragma unroll
-      for (int e = 0; e < RPL; ++e) acc[e] = __builtin_fma(SC::to_double(SC::elem(u[j], e)), a, acc[e]);
-    }
-#pragma unroll
-    for (int e = 0; e < RPL; ++e)
-      if (row0 + e < c.n) out[(int64_t)k * c.ldo + row0 + e] = (TO)acc[e];
+    for (int j = 0; j < RB; ++j) acc = __builtin_fma(SC::to_double(SC::elem(u[j], 0)), A[k * CMAX + j], acc);
+    out[(int64_t)k * c.ldo + row] = (TO)acc;
   }
 }
 
@@ -363,19 +351,16 @@ static int cu_count() {
   return cache[dev] = cus;
 }
 
-int combine_few_blocks(int64_t n, int basis) {
-  const int64_t rows = CB_THREADS * (basis == 0 ? 1 : (basis == 1 ? 2 : 4));
-  return (int)((n + rows - 1) / rows);
-}
+int combine_few_blocks(int64_t n) { return (int)((n + CB_THREADS - 1) / CB_THREADS); }
 
-// Grid of one read-out.  Rows: one thread per 8 bytes of a column.  Else one
+// Grid of one read-out.  Rows: one thread per row.  Else one
 // workgroup per CU in all (two with streaming stores; see the top of the
 // file), shared by the launch's state blocks, with a unit per wavefront at least.  Workgroups go to the
 // eight XCDs in turn by linear index x + g y; with g a multiple of 8 the
 // state blocks of one row share run on the same XCD and read its stored
 // columns through one L2.
-static dim3 combine_grid(const CombineArgs& c, const CombineClass& k, int basis, bool nt) {
-  if (k.kind == KIND_ROWS) return dim3((unsigned)combine_few_blocks(c.n, basis), 1);
+static dim3 combine_grid(const CombineArgs& c, const CombineClass& k, bool nt) {
+  if (k.kind == KIND_ROWS) return dim3((unsigned)combine_few_blocks(c.n), 1);
   const int ur = (k.kind == KIND_FP32 ? 32 : 16) * (CB_THREADS / 64);
   const unsigned ys = (unsigned)((c.K + k.states - 1) / k.states);
   int64_t g = std::min<int64_t>((c.n + ur - 1) / ur, std::max<int64_t>(1, (nt ? 2 : 1) * cu_count() / (int64_t)ys));
@@ -405,7 +390,7 @@ static hipError_t launch_rb(const CombineArgs& c, const dim3& grid, int rb, hipS
 template <typename TS, typename TO, bool NT>
 static hipError_t launch_t(const CombineArgs& c, int basis, int out_f32, int rb, hipStream_t s) {
   const CombineClass k = combine_class(basis, out_f32, c.K);
-  const dim3 grid = combine_grid(c, k, basis, NT);
+  const dim3 grid = combine_grid(c, k, NT);
   if (k.kind == KIND_ROWS) return launch_rb<KIND_ROWS, TS, TO, 1, false>(c, grid, rb, s);
   if constexpr (std::is_same<TO, float>::value && !std::is_same<TS, double>::value) {
     switch (k.ns) {

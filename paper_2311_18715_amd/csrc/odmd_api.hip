@@ -7,7 +7,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <climits>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -1142,8 +1141,8 @@ odmd_status odmd_predict_batch(odmd_t* hs, const int32_t* steps, void* const* ou
     std::vector<FewLaunch> fl;
     for (size_t k = 0; k < few.size(); ++k) {
       odmd_t h = hs[few[k]];
-      const int blocks = combine_few_blocks(h->n, (int)h->basis);
-      if (k == 0 || key(few[k]) != key(few[k - 1]) || fl.back().nblocks > INT_MAX - blocks)
+      const int blocks = combine_few_blocks(h->n);
+      if (k == 0 || key(few[k]) != key(few[k - 1]) || fl.back().nblocks > COMBINE_FEW_BLOCKS - blocks)
         fl.push_back(FewLaunch{(int)k, 0, 0});
       CombineDesc& d = cd[k];
       d = CombineDesc{};

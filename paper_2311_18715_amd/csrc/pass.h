@@ -133,7 +133,8 @@ struct CombineDesc {
   int blk0;             // its first workgroup in the launch
 };
 constexpr int COMBINE_FEW = 4;            // states a batched read-out takes per stream, at most
-int combine_few_blocks(int64_t n, int basis);
+constexpr int COMBINE_FEW_BLOCKS = (1 << 24) - 1;   // workgroups of one launch (fewer than 2^32 threads)
+int combine_few_blocks(int64_t n);
 hipError_t launch_combine_few(const CombineDesc* d, int nd, int nblocks, int basis, int out_f32, int rb,
                               hipStream_t s);
 
