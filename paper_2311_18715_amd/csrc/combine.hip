@@ -353,17 +353,31 @@ static int cu_count() {
 
 int combine_few_blocks(int64_t n) { return (int)((n + CB_THREADS - 1) / CB_THREADS); }
 
-// Grid of one read-out.  Rows: one thread per row.  Else one
-// workgroup per CU in all (two with streaming stores; see the top of the
-// file), shared by the launch's state blocks, with a unit per wavefront at least.  Workgroups go to the
-// eight XCDs in turn by linear index x + g y; with g a multiple of 8 the
-// state blocks of one row share run on the same XCD and read its stored
-// columns through one L2.
+// Grid of one read-out.  Rows: one thread per row.  Else one workgroup per CU
+// in all (two with streaming stores; see the top of the file), shared by the
+// launch's state blocks, with a unit per wavefront at least.  Up to 10 FP64
+// states (16 with streaming stores) of many rows are read bound, not write
+// bound, and want more loads in flight: one workgroup per CU and 32 units a
+// wavefront, at most eight (5 states of 32 columns, n = 1,000,001: 65 us with
+// one per CU, 52 with the two it gets; of 24 columns, n = 2,000,001: 123 and
+// 97).  More of them cost smaller reads (5 of 56 columns, n = 400,001: 38.7 us
+// with one, 44.4 with three) and ragged states beyond that count, which merge
+// better from few writers (16 states of 32 columns, n = 5,000,001: a quarter
+// less time with one than with eight).
+// Workgroups go to the eight XCDs in turn by linear index x + g y; with g a
+// multiple of 8 the state blocks of one row share run on the same XCD and read
+// its stored columns through one L2.
 static dim3 combine_grid(const CombineArgs& c, const CombineClass& k, bool nt) {
   if (k.kind == KIND_ROWS) return dim3((unsigned)combine_few_blocks(c.n), 1);
-  const int ur = (k.kind == KIND_FP32 ? 32 : 16) * (CB_THREADS / 64);
+  const int waves = CB_THREADS / 64, ur = (k.kind == KIND_FP32 ? 32 : 16) * waves;
   const unsigned ys = (unsigned)((c.K + k.states - 1) / k.states);
-  int64_t g = std::min<int64_t>((c.n + ur - 1) / ur, std::max<int64_t>(1, (nt ? 2 : 1) * cu_count() / (int64_t)ys));
+  const int64_t most = (c.n + ur - 1) / ur;             // one unit a wavefront
+  const int64_t cus = cu_count();
+  int64_t per_cu = nt ? 2 : 1;
+  if (k.kind == KIND_FP64 && (c.K <= 10 || (nt && c.K <= 16)))
+    per_cu = std::max(per_cu, std::min<int64_t>(8, (most + 32 * cus - 1) / (32 * cus)));
+  int64_t g = per_cu * cus;
+  g = std::min<int64_t>(most, std::max<int64_t>(1, g / (int64_t)ys));
   if (ys > 1 && g > 8) g = g / 8 * 8;
   return dim3((unsigned)g, ys);
 }

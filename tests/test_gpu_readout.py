@@ -141,3 +141,13 @@ def test_batched_few_states_are_finite():
         for m, states in zip(models, predict_batch(models, [steps] * len(models))):
             assert torch.isfinite(states).all() and states.abs().max() > 0
             assert torch.equal(states, m.predict(steps))
+
+
+@pytest.mark.parametrize("n", [600001, 1100032])
+@pytest.mark.parametrize("steps", [2, 5, 10, 11, 16, 17])
+def test_more_workgroups_for_few_states_of_many_rows(n, steps):
+    """From 524,289 rows up to 10 FP64 states, and from 1,048,577 rows up to 16
+    that start on whole lines (n = 1,100,032), take more workgroups per CU; the
+    counts beyond take the usual ones.  Shares of unequal length either way."""
+    m = model(n, 12, "f64", 16)
+    check(m, m.predict(steps), steps)
