@@ -21,25 +21,29 @@
 // take the FP32 matrix cores instead (128-byte stores); a few states
 // (K <= 4) take one row per lane.
 //
-// The writes bound it, and how they are made decides their rate.  A state's
-// rows start at any multiple of the element size, so a wavefront's piece of
-// a state is usually not whole 128-byte lines.  Streaming (nontemporal)
-// stores send such pieces to memory as partial lines: 100 states of
-// n = 585,732 FP32 rows as bare stores, 1.7 TB/s against 5.4 TB/s with
-// ordinary stores, which merge neighbouring pieces in L2; only where every
-// state starts on a line do they cost nothing (and save a little: 500 FP64
-// states at n = 160,000, 214 against 228 us).  So streaming stores are used
-// only there.  Pieces merge when neighbours are written
-// soon after each other, so few wavefronts write at a time: one workgroup
-// per CU in all, each on a contiguous share of the rows (100 FP32 states,
-// n = 585,732: 112 us with one, 126 with two, 140 with three).  The
-// store addresses step by one 64-bit add each from an opaque start: left
-// to itself the compiler held every state's address in registers (230
-// registers, two waves per SIMD, spills with the next unit's loads in flight).
-// Before and after (streaming stores everywhere, two workgroups per CU):
-// 100 FP32 states, n = 585,732, 178 -> 115 us; FP64, 100 states of n = 160,001
-// 115 -> 56 us, 500 of them 541 -> 294 us; 500 states of n = 160,000 (whole
-// lines) 167 us, as before.
+// The products bound it as long as the writes merge; how they are made decides
+// that.  A state's rows start at any multiple of the element size, so a
+// wavefront's piece of a state is usually not whole 128-byte lines.  Streaming
+// (nontemporal) stores send such pieces to memory as partial lines; ordinary
+// ones merge neighbouring pieces in L2.  Only where every state starts on a
+// line do streaming stores save time, and they are used only there.  Pieces
+// merge when neighbours are written soon after each other, so few wavefronts
+// write at a time: one workgroup per CU in all (two with streaming stores),
+// each on a contiguous share of the rows.  The store addresses step by one
+// 64-bit add each from an opaque start: left to itself the compiler held every
+// state's address in registers (230 registers, two waves per SIMD, spills with
+// the next unit's loads in flight).
+// The whole read-out, kernel trace, 56 columns, us; "none" skips the stores:
+//                                streaming  ordinary  none   before (streaming
+//                                                            everywhere, two
+//                                                            or more per CU)
+//   500 FP64, n = 160,000 (lines)   192        212     180   219
+//   500 FP64, n = 160,001           544        288     190   545
+//   100 FP64, n = 160,001           112         57      54   114
+//   100 FP32, n = 585,732           192        112     107   185
+// and with two and three workgroups per CU, ordinary stores, 500 FP64 states
+// at n = 160,001 337 and 338, 100 FP32 118 and 128.  The products of the first
+// row run at 51 of 78.6 TFLOP/s, of the last at 78 of 157.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
