@@ -1110,6 +1110,12 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   if (tid >= 64 && tid < 128) {
     const int j = tid - 64;
     if (j < r) pvec[j] += p2[j];           // sigma and p1 were staged with Q
+    if (j == 0) {                          // the core's size (step 5): p and rho are at most ||x||
+      const double xx = tot[P_XX];
+      int e = xx > 0.0 ? __builtin_amdgcn_frexp_exp(xx) / 2 : -2000;
+      e = max(e, r > 0 ? __builtin_amdgcn_frexp_exp(ssig[0]) : -2000);
+      si[2] = abs(e) <= 100 || e == -2000 ? 0 : e;
+    }
   } else if (tid >= 128) {
     const int q0 = (tid - 128) >> 4, l16 = tid & 15;
     for (int row = q0; row < CMAX; row += (CORE_THREADS - 128) / 16) {
@@ -1228,7 +1234,22 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
     }
   }
 
-  // 5. SVD of the core: secular equation, one-sided Jacobi if that fails
+  // 5. SVD of the core: secular equation, one-sided Jacobi if that fails.
+  //    Both multiply squares of its entries by squares: a core whose largest
+  //    entry lies outside 2^-100 .. 2^100 (about) is divided by the power of
+  //    two 2^ex that brings it to order one, exactly, and its left vectors,
+  //    scaled to the singular values, are multiplied by it after
+  const int ex = si[2];
+  double rhos = rho;
+  if (ex != 0) {                           // uniform, rare
+    const double down = ldexp(1.0, -ex);
+    rhos *= down;
+    if (tid < r) {
+      ssig[tid] *= down;
+      pvec[tid] *= down;
+    }
+    __syncthreads();
+  }
   int sweeps = 0;
   bool have_norms = false;               // the secular solver left the column norms in sd
   if (gfix) {
@@ -1236,18 +1257,18 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
     for (int idx = tid; idx < M * M; idx += CORE_THREADS) {
       const int i = idx % M, j = idx / M;
       if (j < r) sA[j * LDK + i] = (i < r) ? sA[j * LDK + i] * ssig[j] : 0.0;
-      else sA[j * LDK + i] = (i < r) ? pvec[i] : rho;
+      else sA[j * LDK + i] = (i < r) ? pvec[i] : rhos;
       sV[j * LDK + i] = (i == j) ? 1.0 : 0.0;
     }
     __syncthreads();
     sweeps = jacobi_sweeps(sA, sV, sd, M, &flag);
-  } else if (c.jacobi_only || !secular_svd(sA, sV, ssig, pvec, rho, r, sec, sd, have_norms)) {
+  } else if (c.jacobi_only || !secular_svd(sA, sV, ssig, pvec, rhos, r, sec, sd, have_norms)) {
     have_norms = false;
     for (int idx = tid; idx < M * M; idx += CORE_THREADS) {
       const int i = idx % M, j = idx / M;
       double v;
       if (j < r) v = (i == j) ? ssig[j] : 0.0;
-      else v = (i < r) ? pvec[i] : rho;
+      else v = (i < r) ? pvec[i] : rhos;
       sA[j * LDK + i] = v;
       sV[j * LDK + i] = (i == j) ? 1.0 : 0.0;
     }
@@ -1259,7 +1280,12 @@ __device__ __forceinline__ void core_update(const CoreArgs& c) {
   //    (one 16-lane quarter-wave per column for the norm, M = r + 1 may exceed
   //    the 64 quarter-waves; eight lanes per column for its rank)
   const int qcl = tid & 15;
-  if (!have_norms) {                       // uniform
+  if (!have_norms || ex != 0) {            // uniform
+    if (ex != 0) {
+      __syncthreads();
+      for (int idx = tid; idx < M * M; idx += CORE_THREADS) sA[idx / M * LDK + idx % M] *= ldexp(1.0, ex);
+      __syncthreads();
+    }
     for (int col = tid >> 4; col < M; col += CORE_THREADS / 16) {
       double s = 0.0;
       for (int i = qcl; i < M; i += 16) s = __builtin_fma(sA[col * LDK + i], sA[col * LDK + i], s);

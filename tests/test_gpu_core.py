@@ -90,3 +90,60 @@ def test_no_update_falls_back_to_jacobi(r_max, pairs):
     for j in range(r_max + 14):
         g.update(X[j], Y[j])
         assert g.info().last_sweeps == 0, j
+
+
+@pytest.mark.parametrize("solver", ["secular", "jacobi"])
+@pytest.mark.parametrize("pairs", ["chained", "general"])
+@pytest.mark.parametrize("scale", [1e-140, 1e-100, 1e-60, 1e60, 1e100, 1e140])
+@pytest.mark.parametrize("r_max", [7, 30, 64])
+def test_snapshots_near_the_ends_of_the_exponent_range(r_max, scale, pairs, solver, monkeypatch):
+    """Snapshots whose squares are in range and whose fourth powers are not:
+    both solvers of the core work with squares of its entries times squares.
+    The same bounds as at scale one, relative to the scale."""
+    if solver == "jacobi":
+        monkeypatch.setenv("ODMD_CORE_SVD", "jacobi")
+    rng = np.random.default_rng(500 + r_max)
+    updates = r_max + 14
+    X = rng.standard_normal((900, updates + 1)) * scale
+    Y = rng.standard_normal((900, updates)) * scale if pairs == "general" else X[:, 1:]
+    g = ODMD(900, r_max, 1e-10, pairs=pairs)
+    o = (O.OnlineDMDF1 if pairs == "general" else O.OnlineDMD)(900, r_max, 1e-10)
+    Xd, Yd = (torch.from_numpy(np.ascontiguousarray(A.T)).cuda() for A in (X, Y))
+    for j in range(updates):
+        g.update(Xd[j], Yd[j])
+        o.update(X[:, j], Y[:, j])
+        assert (g.info().last_sweeps == 0) == (solver == "secular"), j
+    g.sync()
+    s = g.state()
+    assert s["r"] == o.r == r_max
+    np.testing.assert_allclose(s["sigma"], o.sigma, rtol=1e-11)
+    U = g.basis_matrix()
+    assert torch.linalg.norm(U.T @ U - torch.eye(r_max, dtype=U.dtype, device=U.device)).item() < 1e-12
+    ref = np.asarray(o.predict(1)).reshape(-1) / scale
+    got = g.predict(1).double().cpu().numpy().reshape(-1) / scale
+    assert np.linalg.norm(got - ref) <= 1e-9 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("pairs", ["chained", "general"])
+@pytest.mark.parametrize("basis,power", [("f64", 400), ("f64", -400), ("f32", 110), ("bf16", 110)])
+@pytest.mark.parametrize("solver", ["secular", "jacobi"])
+def test_powers_of_two_scale_every_result_exactly(basis, power, pairs, solver, monkeypatch):
+    """The core divided by a power of two and multiplied by it again gives the
+    bits of the core at scale one; a BF16 basis takes the general SVD at its
+    refolds.  (FP32's and BF16's residuals would leave their range downwards.)"""
+    if solver == "jacobi":
+        monkeypatch.setenv("ODMD_CORE_SVD", "jacobi")
+    X = torch.from_numpy(np.random.default_rng(3).standard_normal((80, 700))).cuda().to(torch.float64 if basis == "f64" else torch.float32)
+    a, b = (ODMD(700, 20, 1e-10, basis=basis, pairs=pairs) for _ in range(2))
+    Z = X * 2.0 ** power
+    for j in range(60):
+        k = j + 1 if pairs == "chained" else (7 * j + 3) % 80
+        a.update(X[j], X[k])
+        b.update(Z[j], Z[k])
+    a.sync(), b.sync()
+    s, t = a.state(), b.state()
+    assert s["r"] == t["r"] == 20 and a.info().last_sweeps == b.info().last_sweeps
+    assert np.array_equal(s["sigma"], t["sigma"] * 2.0 ** -power)
+    assert np.array_equal(s["atilde"], t["atilde"]) and np.array_equal(s["p_y"], t["p_y"] * 2.0 ** -power)
+    assert torch.equal(a.basis_matrix(), b.basis_matrix())
+    assert torch.equal(a.predict(6), b.predict(6) * 2.0 ** -power)
