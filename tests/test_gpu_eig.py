@@ -79,7 +79,7 @@ def decoupled(r, c, scale, seed=23):
     return m
 
 
-@pytest.mark.parametrize("r", [4, 6, 7, 21, 40])
+@pytest.mark.parametrize("r", [2, 3, 4, 6, 7, 21, 40, 64])
 @pytest.mark.parametrize("c,scale", [(1.0, 1.0), (1e-56, 1.0), (1e-60, 1.0), (1e-67, 1.0), (1e-69, 1.0), (1e-80, 1.0), (1e-120, 1.0), (1e-135, 1.0),
                                      (1e-145, 1.0), (1e-180, 1e100), (1e-230, 1e120)])
 def test_eigenvalues_of_a_block_far_below_the_rest(r, c, scale):
